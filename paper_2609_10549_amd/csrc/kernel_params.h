@@ -16,13 +16,13 @@ constexpr int kCtrlExit = kMaxQueues;       // ctrl word: exit counter
 constexpr int kTraceWords = 8;       // words per tile-trace record
 constexpr int kCuSlots = 8 * 256;    // ctrl words: per (XCC, SE/SH/CU id) slot claims
 constexpr int kMaxSplitTiles = 512;  // tiles of a split-K launch (one counter each)
-constexpr int kMaxSplit = 16;        // K slices per tile
+constexpr int kMaxSplit = 8;         // K slices per tile (the finisher has an instance per count)
 constexpr uint64_t kTileSpanMax = 1ull << 30;   // bytes of A, W or P one tile may span
 
 // Tile configurations of the GEMM kernel.
 enum TileCfg : int {
-    kTile256 = 0,   // 256 x 256 output tile, 128 KiB LDS, one workgroup per CU
-    kTile128 = 1,   // 128 x 128 output tile, 64 KiB LDS, two workgroups per CU
+    kTile256 = 0,   // 256 x 256 output tile, 160 KiB LDS, one workgroup per CU
+    kTile128 = 1,   // 128 x 128 output tile, 80 KiB LDS, two workgroups per CU
 };
 inline int tile_rows(int cfg) { return cfg == kTile256 ? 256 : 128; }
 inline int tile_cols(int cfg) { return cfg == kTile256 ? 256 : 128; }

@@ -180,11 +180,14 @@ __device__ __forceinline__ int ticket_position(const GemmParams &p, int v, uint3
     return (v + p.nq * k) * p.q_size + i;
 }
 
-// s_waitcnt vmcnt(VM) lgkmcnt(0), expcnt untouched (gfx9 encoding)
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+
+// At most VM vector-memory operations (and no LDS read) still in flight.
 template <int VM>
 __device__ __forceinline__ void wait_vm_lgkm0() {
     static_assert(VM >= 0 && VM < 64, "vmcnt range");
-    __builtin_amdgcn_s_waitcnt((VM & 15) | ((VM >> 4) << 14) | (7 << 4));
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(VM) : "memory");
 }
 
 // Workgroup barrier with no memory fence: the caller has already waited for
@@ -193,32 +196,55 @@ __device__ __forceinline__ void wait_vm_lgkm0() {
 __device__ __forceinline__ void lds_barrier() {
     __builtin_amdgcn_sched_barrier(0);
     __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
 }
 
-// CNT global -> LDS loads (16 bytes per lane, 1 KiB per wave and load) of one
-// operand into the 1 KiB blocks (q0 + j) * 4 + wave of `lds`.
-template <int CNT>
-__device__ __forceinline__ void load_blocks(__amdgpu_buffer_rsrc_t rsrc, char *lds, const uint32_t *off, int q0,
-                                            uint32_t kc2, int wave) {
-#pragma unroll
-    for (int j = 0; j < CNT; ++j)
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, LDS_AS(lds + ((q0 + j) * 4 + wave) * 1024), 16,
-                                                 off[q0 + j] + kc2, 0, 0, 0);
+// Buffer resource words of tile_rsrc as plain scalars, for dma16.
+__device__ __forceinline__ i32x4 tile_rsrc4(const void *base, uint64_t total, uint64_t off) {
+    const uint64_t left = total > off ? total - off : 0;
+    const uint32_t bound = (uint32_t)(left < kTileSpanMax ? left : kTileSpanMax);
+    const uint64_t a = (uint64_t)base + off;
+    i32x4 r;
+    r[0] = __builtin_amdgcn_readfirstlane((int)(uint32_t)a);
+    r[1] = __builtin_amdgcn_readfirstlane((int)((uint32_t)(a >> 32) & 0xFFFFu));
+    r[2] = __builtin_amdgcn_readfirstlane((int)bound);
+    r[3] = 0x00020000;
+    return r;
 }
 
-// Fragments of MFMA substep kk of the stage in (sA, sW): ROWB-byte rows,
-// 16-byte chunk c of row r stored at chunk c ^ swz.
-template <int FM, int FN, int ROWB>
-__device__ __forceinline__ void read_frags(const char *sA, const char *sW, int r, int swz, int kk, int hi, int wm0,
-                                           int wn0, bf16x8 (&a)[FM], bf16x8 (&b)[FN]) {
+// One global -> LDS load: 16 bytes per lane from rsrc + voff to LDS byte
+// address lds + 16 * lane. It has no register result, so nothing of it is
+// live in a register while it is in flight; it is written as an instruction
+// because the compiler, which cannot see that two halves of one LDS array
+// are different buffers, would otherwise wait for every load in flight before
+// each LDS read. The waits are wait_vm_lgkm0's, counted where they are made.
+// (s_nop: a scalar write of M0 needs a wait state before the load reads it.)
+__device__ __forceinline__ void dma16(i32x4 rsrc, uint32_t voff, uint32_t lds) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+                 :
+                 : "s"(lds), "v"(voff), "s"(rsrc)
+                 : "memory");
+}
+
+// `CNT` loads of one operand into the 1 KiB blocks j * 4 + wave of the LDS
+// buffer at `lds`.
+template <int CNT>
+__device__ __forceinline__ void load_blocks(i32x4 rsrc, uint32_t lds, const uint32_t *off, uint32_t kc2, int wave) {
+#pragma unroll
+    for (int j = 0; j < CNT; ++j) dma16(rsrc, off[j] + kc2, lds + (uint32_t)((j * 4 + wave) * 1024));
+}
+
+// Fragments of MFMA substep kk: 128-byte rows, 16-byte chunk c of row r
+// stored at chunk c ^ swz; fa / fw: this lane's row in the stage's buffers.
+template <int FM, int FN>
+__device__ __forceinline__ void read_frags(const char *fa, const char *fw, int swz, int kk, int hi, bf16x8 (&a)[FM],
+                                           bf16x8 (&b)[FN]) {
     const int coff = ((2 * kk + hi) ^ swz) << 4;
 #pragma unroll
-    for (int mi = 0; mi < FM; ++mi)
-        a[mi] = *reinterpret_cast<const bf16x8 *>(sA + (wm0 + mi * 32 + r) * ROWB + coff);
+    for (int mi = 0; mi < FM; ++mi) a[mi] = *reinterpret_cast<const bf16x8 *>(fa + coff + mi * 32 * 128);
 #pragma unroll
-    for (int ni = 0; ni < FN; ++ni)
-        b[ni] = *reinterpret_cast<const bf16x8 *>(sW + (wn0 + ni * 32 + r) * ROWB + coff);
+    for (int ni = 0; ni < FN; ++ni) b[ni] = *reinterpret_cast<const bf16x8 *>(fw + coff + ni * 32 * 128);
 }
 
 // MFMAs [I0, I0 + CNT) of a substep (block i: acc[i / FM][i % FM]).
@@ -227,6 +253,22 @@ __device__ __forceinline__ void mfma_range(f32x16 (&acc)[FN][FM], const bf16x8 (
 #pragma unroll
     for (int i = I0; i < I0 + CNT; ++i)
         acc[i / FM][i % FM] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[i / FM], a[i % FM], acc[i / FM][i % FM], 0, 0, 0);
+}
+
+// MFMAs [I0, I0 + CNT) with the stage loads [0, L) of one operand spread
+// between them, in this order.
+template <int I0, int CNT, int L, int FM, int FN>
+__device__ __forceinline__ void mfma_loads(f32x16 (&acc)[FN][FM], const bf16x8 (&a)[FM], const bf16x8 (&b)[FN],
+                                           i32x4 rsrc, uint32_t lds, const uint32_t *off, uint32_t kc2, int wave) {
+#pragma unroll
+    for (int i = 0; i < CNT; ++i) {
+        const int k = I0 + i;
+        acc[k / FM][k % FM] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[k / FM], a[k % FM], acc[k / FM][k % FM], 0, 0, 0);
+#pragma unroll
+        for (int j = i * L / CNT; j < (i + 1) * L / CNT; ++j)
+            dma16(rsrc, off[j] + kc2, lds + (uint32_t)((j * 4 + wave) * 1024));
+        __builtin_amdgcn_sched_barrier(0);
+    }
 }
 
 // Scheduling groups for the CNT MFMAs just emitted: one instruction of class
@@ -244,53 +286,9 @@ __device__ __forceinline__ void interleave() {
     __builtin_amdgcn_sched_barrier(0);
 }
 
-constexpr int kDsRead = 0x100, kVmemRead = 0x020;
+constexpr int kDsRead = 0x100;
 
 constexpr int kBK = 64;   // K depth of one LDS stage
-
-// ---- the pipeline: two LDS stages of K = 64, barrier before the last substep
-// Stage s on (cA, cW), substep-0 fragments in (a0, b0). Substep 0 issues the
-// W loads of stage s + 1 into (nA, nW) (its A loads went out in stage s - 1);
-// substep 3 waits for all of stage s + 1, joins the barrier, reads stage
-// s + 1's first fragments and issues the A loads of stage s + 2 into
-// (cA, cW), which no wave reads any more.
-template <int BM, int BN, int FM, int FN>
-__device__ __forceinline__ void stage2e(char *cA, char *cW, char *nA, char *nW, f32x16 (&acc)[FN][FM],
-                                        bf16x8 (&a0)[FM], bf16x8 (&b0)[FN], bf16x8 (&a1)[FM], bf16x8 (&b1)[FN],
-                                        __amdgpu_buffer_rsrc_t rA, __amdgpu_buffer_rsrc_t rW, const uint32_t *offA,
-                                        const uint32_t *offW, uint32_t kc2_next, uint32_t kc2_next2, int r, int swz,
-                                        int hi, int wm0, int wn0, int wave) {
-    constexpr int NM = FM * FN, H = NM / 2, ND = FM + FN;
-    constexpr int L = BM / 32;   // loads per wave and operand per stage
-    // substep 0
-    read_frags<FM, FN, 128>(cA, cW, r, swz, 1, hi, wm0, wn0, a1, b1);
-    mfma_range<0, H, FM, FN>(acc, a0, b0);
-    interleave<H, kDsRead, ND>();
-    load_blocks<L>(rW, nW, offW, 0, kc2_next, wave);
-    mfma_range<H, NM - H, FM, FN>(acc, a0, b0);
-    interleave<NM - H, kVmemRead, L>();
-    // substep 1
-    read_frags<FM, FN, 128>(cA, cW, r, swz, 2, hi, wm0, wn0, a0, b0);
-    mfma_range<0, H, FM, FN>(acc, a1, b1);
-    interleave<H, kDsRead, ND>();
-    mfma_range<H, NM - H, FM, FN>(acc, a1, b1);
-    interleave<NM - H, kVmemRead, 0>();
-    // substep 2
-    read_frags<FM, FN, 128>(cA, cW, r, swz, 3, hi, wm0, wn0, a1, b1);
-    mfma_range<0, H, FM, FN>(acc, a0, b0);
-    interleave<H, kDsRead, ND>();
-    mfma_range<H, NM - H, FM, FN>(acc, a0, b0);
-    interleave<NM - H, kVmemRead, 0>();
-    // substep 3
-    wait_vm_lgkm0<0>();
-    lds_barrier();
-    read_frags<FM, FN, 128>(nA, nW, r, swz, 0, hi, wm0, wn0, a0, b0);
-    mfma_range<0, H, FM, FN>(acc, a1, b1);
-    interleave<H, kDsRead, ND>();
-    load_blocks<L>(rA, cA, offA, 0, kc2_next2, wave);
-    mfma_range<H, NM - H, FM, FN>(acc, a1, b1);
-    interleave<NM - H, kVmemRead, L>();
-}
 
 // RS = false: optional main-loop gate (AllGather), plain store.
 // RS = true: optional epilogue gate, fp32 partial add, chunk-done signalling;
@@ -301,15 +299,17 @@ __global__ __launch_bounds__(kThreads, BM == 256 ? 1 : 2)
 void gemm_kernel(const GemmParams p) {
     constexpr int WM = BM / 2, WN = BN / 2;
     constexpr int FM = WM / 32, FN = WN / 32;
-    constexpr int NOFF = BM / 32;   // loads per wave, operand and stage
-    static_assert(BM == BN && BM * 128 >= 16384, "square tiles; stage buffers hold the epilogue patches");
-    __shared__ __attribute__((aligned(1024))) char sA0[BM * 128];
-    __shared__ __attribute__((aligned(1024))) char sA1[BM * 128];
-    __shared__ __attribute__((aligned(1024))) char sW0[BN * 128];
-    __shared__ __attribute__((aligned(1024))) char sW1[BN * 128];
-    __shared__ int s_pos;
-    __shared__ int s_ok;
-    __shared__ int s_last;
+    constexpr int LA = BM / 32, LW = BN / 32;   // loads per wave and stage of A, W
+    constexpr int SA = BM * 128, SW = BN * 128; // bytes of one stage buffer
+    static_assert(SA >= 16384 && SW >= 16384, "stage buffers hold the epilogue's partial blocks");
+    // three A buffers, then two W buffers
+    __shared__ __attribute__((aligned(1024))) char smem[3 * SA + 2 * SW];
+    // control words in the tail of the third A buffer: the first load that
+    // lands there is issued in stage 0 of a tile, behind the prologue's
+    // barrier, which every wave reaches after it read them
+    int &s_pos = reinterpret_cast<int *>(smem + 3 * SA)[-1];
+    int &s_ok = reinterpret_cast<int *>(smem + 3 * SA)[-2];
+    int &s_last = reinterpret_cast<int *>(smem + 3 * SA)[-3];
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -346,7 +346,7 @@ void gemm_kernel(const GemmParams p) {
         s_pos = pos;
     }
     __syncthreads();
-    int pos = s_pos;
+    int pos = __builtin_amdgcn_readfirstlane(s_pos);
 
     while (pos < total) {
         // work position -> (tile position, K slice); `split`: this tile's K
@@ -392,13 +392,16 @@ void gemm_kernel(const GemmParams p) {
             // stores are dropped
             // A from the tile's first (mapped) row, W from its first column
             const int row0 = map_row(p, m0);
-            const __amdgpu_buffer_rsrc_t rA = tile_rsrc(p.A, p.a_bytes, (uint64_t)row0 * (uint64_t)p.lda * 2u);
-            const __amdgpu_buffer_rsrc_t rW = tile_rsrc(p.W, p.w_bytes, (uint64_t)n0 * (uint64_t)p.ldw * 2u);
-            uint32_t offA[NOFF], offW[NOFF];
+            const i32x4 rA0 = tile_rsrc4(p.A, p.a_bytes, (uint64_t)row0 * (uint64_t)p.lda * 2u);
+            const i32x4 rW0 = tile_rsrc4(p.W, p.w_bytes, (uint64_t)n0 * (uint64_t)p.ldw * 2u);
+            uint32_t offA[LA], offW[LW];
 #pragma unroll
-            for (int q = 0; q < NOFF; ++q) {
+            for (int q = 0; q < LA; ++q) {
                 const int ia = m0 + 32 * q + lrow0;
                 offA[q] = ia < p.M ? (uint32_t)(map_row(p, ia) - row0) * (uint32_t)p.lda * 2u : kOOBRow;
+            }
+#pragma unroll
+            for (int q = 0; q < LW; ++q) {
                 const int iw = n0 + 32 * q + lrow0;
                 offW[q] = iw < p.N ? (uint32_t)(iw - n0) * (uint32_t)p.ldw * 2u : kOOBRow;
             }
@@ -406,27 +409,69 @@ void gemm_kernel(const GemmParams p) {
                 const int kc = kb + st * kBK + cchunk * 8;
                 return kc < ke ? (uint32_t)kc * 2u : kOOBCol;
             };
-            // an even stage count keeps the unrolled loop free of early exits
-            // (padding stages read only out-of-range columns, i.e. zeros)
-            const int KT = (((ke - kb + kBK - 1) / kBK) + 1) & ~1;
-            // prologue: stage 0 and the A half of stage 1 in flight; stage 0
-            // landed, its first fragments read
-            load_blocks<NOFF>(rA, sA0, offA, 0, kcol(0), wave);
-            load_blocks<NOFF>(rW, sW0, offW, 0, kcol(0), wave);
-            load_blocks<NOFF>(rA, sA1, offA, 0, kcol(1), wave);
-            wait_vm_lgkm0<NOFF>();
+            const int KT = (ke - kb + kBK - 1) / kBK;
+            // LDS byte offsets: A of this stage, the next, the one after;
+            // W of this stage, the next
+            const uint32_t lds0 = (uint32_t)(uintptr_t)LDS_AS(smem);
+            uint32_t aC = lds0, aN = aC + SA, aF = aN + SA, wC = aF + SA, wN = wC + SW;
+            // prologue: stages 0 and 1 in flight; stage 0 landed, its first
+            // fragments read (s_nop: resource words that came out of vector
+            // registers need five wait states before a load reads them)
+            i32x4 rA = rA0, rW = rW0;
+            asm volatile("s_nop 4" : "+s"(rA), "+s"(rW));
+            load_blocks<LA>(rA, aC, offA, kcol(0), wave);
+            load_blocks<LW>(rW, wC, offW, kcol(0), wave);
+            load_blocks<LA>(rA, aN, offA, kcol(1), wave);
+            load_blocks<LW>(rW, wN, offW, kcol(1), wave);
+            wait_vm_lgkm0<LA + LW>();
             lds_barrier();
             bf16x8 a0[FM], b0[FN], a1[FM], b1[FN];
-            read_frags<FM, FN, 128>(sA0, sW0, r, swz, 0, hi, wm0, wn0, a0, b0);
-            for (int st = 0; st < KT; st += 2) {
-                stage2e<BM, BN, FM, FN>(sA0, sW0, sA1, sW1, acc, a0, b0, a1, b1, rA, rW, offA, offW, kcol(st + 1),
-                                        kcol(st + 2), r, swz, hi, wm0, wn0, wave);
-                stage2e<BM, BN, FM, FN>(sA1, sW1, sA0, sW0, acc, a0, b0, a1, b1, rA, rW, offA, offW, kcol(st + 2),
-                                        kcol(st + 3), r, swz, hi, wm0, wn0, wave);
+            const char *fa = smem + (wm0 + r) * 128;       // this lane's fragment rows, relative
+            const char *fw = smem + (wn0 + r) * 128;       // to a buffer at smem + 0
+            read_frags<FM, FN>(fa + (aC - lds0), fw + (wC - lds0), swz, 0, hi, a0, b0);
+            constexpr int NM = FM * FN, H = NM / 2, ND = FM + FN;
+            // Stage st on (aC, wC), its substep-0 fragments in (a0, b0), stage
+            // st + 1 in flight or landed in (aN, wN). Substep 0 issues the A
+            // loads of stage st + 2 into aF, which stage st - 1 freed; substep 3
+            // waits for all of stage st + 1 (the A loads just issued stay in
+            // flight), joins the barrier, reads stage st + 1's first fragments
+            // and issues the W loads of stage st + 2 into wC, whose fragments
+            // every wave has read by then.
+            for (int st = 0; st < KT; ++st) {
+                const char *ca = fa + (aC - lds0), *cw = fw + (wC - lds0);
+                const uint32_t kc2 = kcol(st + 2);
+                // substep 0
+                read_frags<FM, FN>(ca, cw, swz, 1, hi, a1, b1);
+                mfma_range<0, H, FM, FN>(acc, a0, b0);
+                interleave<H, kDsRead, ND>();
+                mfma_loads<H, NM - H, LA, FM, FN>(acc, a0, b0, rA, aF, offA, kc2, wave);
+                // substep 1
+                read_frags<FM, FN>(ca, cw, swz, 2, hi, a0, b0);
+                mfma_range<0, H, FM, FN>(acc, a1, b1);
+                interleave<H, kDsRead, ND>();
+                mfma_range<H, NM - H, FM, FN>(acc, a1, b1);
+                __builtin_amdgcn_sched_barrier(0);
+                // substep 2
+                read_frags<FM, FN>(ca, cw, swz, 3, hi, a1, b1);
+                mfma_range<0, H, FM, FN>(acc, a0, b0);
+                interleave<H, kDsRead, ND>();
+                mfma_range<H, NM - H, FM, FN>(acc, a0, b0);
+                __builtin_amdgcn_sched_barrier(0);
+                // substep 3
+                wait_vm_lgkm0<LA>();
+                lds_barrier();
+                read_frags<FM, FN>(fa + (aN - lds0), fw + (wN - lds0), swz, 0, hi, a0, b0);
+                mfma_range<0, H, FM, FN>(acc, a1, b1);
+                interleave<H, kDsRead, ND>();
+                mfma_loads<H, NM - H, LW, FM, FN>(acc, a1, b1, rW, wC, offW, kc2, wave);
+                const uint32_t t = aC;
+                aC = aN; aN = aF; aF = t;
+                const uint32_t u = wC;
+                wC = wN; wN = u;
             }
             // the loads issued past the end (zeros) land before the buffers
             // are reused
-            __builtin_amdgcn_s_waitcnt(0);
+            wait_vm_lgkm0<0>();
             __syncthreads();
         }
 
@@ -437,36 +482,12 @@ void gemm_kernel(const GemmParams p) {
             s_pos = ticket_position(p, v, c);
         }
 
-        // Each 32 x 32 fp32 block of the accumulators goes through a per-wave
-        // 4 KiB LDS patch (rows of 128 bytes, 16-byte chunks XOR-permuted by
-        // row & 7) and comes back row-contiguous: 8 lanes per row hold 128
-        // contiguous bytes. `emit(tile row, tile column, 4 values)`.
-        char *patch = sA0 + wave * 4096;
-        auto through_patch = [&](auto &&emit) {
-            const int rr = lane >> 3;          // read-back row within 8
-            const int rc = lane & 7;           // read-back chunk (4 floats)
-#pragma unroll
-            for (int mi = 0; mi < FM; ++mi) {
-#pragma unroll
-                for (int ni = 0; ni < FN; ++ni) {
-#pragma unroll
-                    for (int g = 0; g < 4; ++g) {
-                        const int cc = 2 * g + hi;
-                        f32x4 v4 = {acc[ni][mi][4 * g + 0], acc[ni][mi][4 * g + 1],
-                                    acc[ni][mi][4 * g + 2], acc[ni][mi][4 * g + 3]};
-                        *reinterpret_cast<f32x4 *>(patch + r * 128 + ((cc ^ (r & 7)) << 4)) = v4;
-                    }
-                    __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0): patch written
-#pragma unroll
-                    for (int it = 0; it < 4; ++it) {
-                        const int row = rr + 8 * it;
-                        const f32x4 x = *reinterpret_cast<const f32x4 *>(patch + row * 128 + ((rc ^ (row & 7)) << 4));
-                        emit(wm0 + mi * 32 + row, wn0 + ni * 32 + 4 * rc, x);
-                    }
-                    __builtin_amdgcn_s_waitcnt(0xC07F);   // patch read before reuse
-                }
-            }
-        };
+        // thread coordinates the compiler cannot see to be the same for every
+        // tile: addresses derived from them are computed where they are used,
+        // not kept (spilled) over the main loop
+        int et = tid;
+        asm volatile("" : "+v"(et));
+        const int er = et & 31, ehi = (et >> 5) & 1;
         const int mlim = failed ? 0 : p.M;   // a failed tile stores nothing
         // the tile's partial sum: from P, or, for the rows of an aliased
         // range (a whole number of tiles), from that range's own buffer
@@ -487,22 +508,34 @@ void gemm_kernel(const GemmParams p) {
         // system-scope write-through, so that no L2 write-back is needed
         // before the copy engines read it
         const bool wt = RS && p.done_host != nullptr && (touch & p.send_mask) != 0;
-        // bf16 store of 4 values at tile (row, col), after adding the fp32
-        // partial sum (ReduceScatter): 64 contiguous bytes of C per row
-        auto store4 = [&](int row, int col, float v0, float v1, float v2, float v3, bool add_p) {
-            const int m = m0 + row, n = n0 + col;
+        // 8 consecutive columns of row m from n, 16 bytes of C
+        auto store8 = [&](int m, int n, u32x4 o) {
             if (m < mlim && n < p.N) {
-                const int pm = map_row(p, m);
-                if (add_p) {
-                    const f32x4 pv = *reinterpret_cast<const f32x4 *>(pbase + (size_t)(pm - plo) * p.ldp + n);
-                    v0 += pv[0]; v1 += pv[1]; v2 += pv[2]; v3 += pv[3];
+                uint16_t *dst = p.C + (size_t)map_row(p, m) * p.ldc + n;
+                if (wt) {   // written through to memory: the copy engines read it
+                    __hip_atomic_store(reinterpret_cast<uint64_t *>(dst), (uint64_t)o[0] | ((uint64_t)o[1] << 32),
+                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+                    __hip_atomic_store(reinterpret_cast<uint64_t *>(dst) + 1, (uint64_t)o[2] | ((uint64_t)o[3] << 32),
+                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+                } else {
+                    *reinterpret_cast<u32x4 *>(dst) = o;
                 }
-                const uint64_t o = (uint64_t)pack_bf16x2(v0, v1) | ((uint64_t)pack_bf16x2(v2, v3) << 32);
-                uint64_t *dst = reinterpret_cast<uint64_t *>(p.C + (size_t)pm * p.ldc + n);
-                if (wt)   // written through to memory: the copy engines read it
-                    __hip_atomic_store(dst, o, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-                else
-                    *dst = o;
+            }
+        };
+        // Of a 32 x 32 block in the accumulators' layout, lane (r, hi) holds
+        // row r, columns 8 g + 4 hi + 0..3 as values 4 g + 0..3. Exchanging the
+        // packed pairs of groups 2 j and 2 j + 1 between the two halves of the
+        // wave leaves each lane 8 consecutive columns, 16 j + 8 hi.
+        auto store_block = [&](int mi, int ni, const float (&x)[16]) {
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const float *y = x + 8 * j;
+                const u32x2 s0 =
+                    __builtin_amdgcn_permlane32_swap(pack_bf16x2(y[0], y[1]), pack_bf16x2(y[4], y[5]), false, false);
+                const u32x2 s1 =
+                    __builtin_amdgcn_permlane32_swap(pack_bf16x2(y[2], y[3]), pack_bf16x2(y[6], y[7]), false, false);
+                store8(m0 + wm0 + mi * 32 + er, n0 + wn0 + ni * 32 + 16 * j + 8 * ehi,
+                       u32x4{s0[0], s1[0], s0[1], s1[1]});
             }
         };
         const bool has_p = RS && p.P != nullptr;
@@ -512,10 +545,18 @@ void gemm_kernel(const GemmParams p) {
         // slice order, so the result does not depend on which one was last
         bool finish = true;
         if (split) {
-            float *ws = p.split_ws + (size_t)(wsf + slice) * (BM * BN);
-            through_patch([&](int row, int col, f32x4 x) {
-                *reinterpret_cast<f32x4 *>(ws + row * BN + col) = x;
-            });
+            // in the accumulators' own layout: 4 consecutive values of every
+            // thread of the workgroup, 4 KiB contiguous per store
+            f32x4 *ws = reinterpret_cast<f32x4 *>(p.split_ws + (size_t)(wsf + slice) * (BM * BN)) + et;
+#pragma unroll
+            for (int ni = 0; ni < FN; ++ni)
+#pragma unroll
+                for (int mi = 0; mi < FM; ++mi)
+#pragma unroll
+                    for (int g = 0; g < 4; ++g)
+                        ws[((ni * FM + mi) * 4 + g) * kThreads] =
+                            f32x4{acc[ni][mi][4 * g + 0], acc[ni][mi][4 * g + 1], acc[ni][mi][4 * g + 2],
+                                  acc[ni][mi][4 * g + 3]};
             // The workspace is uncached device memory: a store acknowledged
             // to the wave is in memory, visible to every XCD, and loads read
             // memory. So ordering needs no cache maintenance: each wave waits
@@ -546,149 +587,179 @@ void gemm_kernel(const GemmParams p) {
 
         if (finish) {
             if (split) {
-                const float *ws0 = p.split_ws + (size_t)wsf * (BM * BN);
-                // B elements of 4 per thread at a time, all their slices' loads
-                // (and the partial sum's) in flight at once, then each summed in
-                // slice order: the workspace is uncached, so every load costs a
-                // memory round trip, and B x S of them overlap. With the slice
-                // count a compile-time constant (EX) the loads carry no branch,
-                // and the waits before the sums count them exactly; otherwise
-                // S is an upper bound and slices from ns on are skipped.
-                auto finish_split = [&](auto b_const, auto s_const, auto ex_const) {
+                const f32x4 *ws0 = reinterpret_cast<const f32x4 *>(p.split_ws + (size_t)wsf * (BM * BN)) + et;
+                // B 32 x 32 blocks at a time, all their slices' loads (and the
+                // partial sum's) in flight at once, then each summed in slice
+                // order: the workspace is uncached, so every load costs a memory
+                // round trip, and 4 B S of them overlap. With the slice count a
+                // compile-time constant (EX) the loads carry no branch, and the
+                // waits before the sums count them exactly; otherwise S is an
+                // upper bound and slices from ns on are skipped.
+                auto finish_split = [&](auto b_const, auto s_const) {
                     constexpr int B = decltype(b_const)::value, S = decltype(s_const)::value;
-                    constexpr bool EX = decltype(ex_const)::value;
-                    constexpr int E = BM * BN / 4;
-                    static_assert(E % (kThreads * B) == 0, "whole batches");
-                    for (int e0 = tid; e0 < E; e0 += kThreads * B) {
-                        f32x4 part[B][S];
-                        f32x4 pv[B];
+                    static_assert((FM * FN) % B == 0, "whole batches");
+#pragma unroll 1
+                    for (int blk0 = 0; blk0 < FM * FN; blk0 += B) {
+                        f32x4 part[B][4][S];
+                        f32x4 pv[B][4];
 #pragma unroll
                         for (int b = 0; b < B; ++b) {
-                            const int e = e0 + b * kThreads;
-                            const int row = e / (BN / 4), col = (e - row * (BN / 4)) * 4;
+                            const int blk = blk0 + b, ni = blk / FM, mi = blk % FM;
 #pragma unroll
-                            for (int jj = 0; jj < S; ++jj)
-                                if (EX || jj < ns)
-                                    part[b][jj] = *reinterpret_cast<const f32x4 *>(ws0 + (size_t)jj * (BM * BN) +
-                                                                                    row * BN + col);
-                            pv[b] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-                            const int m = m0 + row, n = n0 + col;
-                            if (has_p && m < p.M && n < p.N)
-                                pv[b] = *reinterpret_cast<const f32x4 *>(pbase + (size_t)(map_row(p, m) - plo) * p.ldp +
-                                                                         n);
+                            for (int g = 0; g < 4; ++g)
+#pragma unroll
+                                for (int jj = 0; jj < S; ++jj)
+                                    part[b][g][jj] = ws0[(size_t)jj * (BM * BN / 4) + (blk * 4 + g) * kThreads];
+                            const int m = m0 + wm0 + mi * 32 + er;
+#pragma unroll
+                            for (int g = 0; g < 4; ++g) {
+                                const int n = n0 + wn0 + ni * 32 + 8 * g + 4 * ehi;
+                                pv[b][g] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+                                if (has_p && m < p.M && n < p.N)
+                                    pv[b][g] = *reinterpret_cast<const f32x4 *>(
+                                        pbase + (size_t)(map_row(p, m) - plo) * p.ldp + n);
+                            }
                         }
 #pragma unroll
                         for (int b = 0; b < B; ++b) {
-                            const int e = e0 + b * kThreads;
-                            const int row = e / (BN / 4), col = (e - row * (BN / 4)) * 4;
-                            f32x4 sum = part[b][0];
+                            const int blk = blk0 + b, ni = blk / FM, mi = blk % FM;
+                            float x[16];
 #pragma unroll
-                            for (int jj = 1; jj < S; ++jj)
-                                if (EX || jj < ns) {
-                                    sum[0] += part[b][jj][0]; sum[1] += part[b][jj][1];
-                                    sum[2] += part[b][jj][2]; sum[3] += part[b][jj][3];
-                                }
-                            store4(row, col, sum[0] + pv[b][0], sum[1] + pv[b][1], sum[2] + pv[b][2],
-                                   sum[3] + pv[b][3], false);
+                            for (int g = 0; g < 4; ++g) {
+                                f32x4 sum = part[b][g][0];
+#pragma unroll
+                                for (int jj = 1; jj < S; ++jj)
+                                    sum += part[b][g][jj];
+#pragma unroll
+                                for (int e = 0; e < 4; ++e) x[4 * g + e] = sum[e] + pv[b][g][e];
+                            }
+                            store_block(mi, ni, x);
                         }
                     }
                 };
                 // The host splits a tile into 2 to 8 slices (more only through
-                // kMaxSplit): each count has its own branch-free instance. Batches
-                // of 4 elements (2 from 5 slices on, and in the ReduceScatter
-                // variant, whose partial-sum epilogue leaves fewer registers) keep
-                // the loads within the registers the main loop leaves, with no
-                // spills.
-                constexpr int BL = RS ? 2 : 4;
-                using yes = std::true_type;
-                using no = std::false_type;
+                // kMaxSplit): each count has its own branch-free instance, with
+                // batches that keep the loads within the registers the main loop
+                // leaves.
                 using std::integral_constant;
                 switch (ns) {
-                case 2: finish_split(integral_constant<int, BL>{}, integral_constant<int, 2>{}, yes{}); break;
-                case 3: finish_split(integral_constant<int, BL>{}, integral_constant<int, 3>{}, yes{}); break;
-                case 4: finish_split(integral_constant<int, BL>{}, integral_constant<int, 4>{}, yes{}); break;
-                case 5: finish_split(integral_constant<int, 2>{}, integral_constant<int, 5>{}, yes{}); break;
-                case 6: finish_split(integral_constant<int, 2>{}, integral_constant<int, 6>{}, yes{}); break;
-                case 7: finish_split(integral_constant<int, 2>{}, integral_constant<int, 7>{}, yes{}); break;
-                case 8: finish_split(integral_constant<int, 2>{}, integral_constant<int, 8>{}, yes{}); break;
-                default:
-                    finish_split(integral_constant<int, BL / 2>{}, integral_constant<int, kMaxSplit>{}, no{});
-                }
-            } else if (has_p) {
-                // as through_patch, with each 32 x 32 block's fp32 partial
-                // brought into LDS by buffer_load ... lds two blocks ahead of
-                // its use, into three 4 KiB buffers per wave, one in each of
-                // the freed stage buffers sA1, sW0 and sW1. C goes out through
-                // buffer stores that the buffer bound drops for rows or
-                // columns outside C (or all of a failed tile), so every block
-                // issues the same memory operations and the wait for a
-                // block's partial lets the two later blocks' loads and the
-                // stores in between stay in flight (with one block ahead, or
-                // with stores skipped by a branch, it waited for all of them:
-                // the epilogue took 17 us per 256 x 256 tile at any number of
-                // workgroups, against 7 us without a partial)
-                constexpr int NB = FM * FN;
-                constexpr int NSLOT = 3, AHEAD = NSLOT - 1;
-                const int prow0 = map_row(p, m0);
-                const __amdgpu_buffer_rsrc_t rP =
-                    tile_rsrc(pbase, pbytes, (uint64_t)(prow0 - plo) * (uint64_t)p.ldp * 4u);
-                const int rr = lane >> 3, rc = lane & 7;
-                char *const pslot[NSLOT] = {sA1 + wave * 4096, sW0 + wave * 4096, sW1 + wave * 4096};
-                const __amdgpu_buffer_rsrc_t rC =
-                    tile_rsrc(p.C, p.c_bytes, (uint64_t)prow0 * (uint64_t)p.ldc * 2u);
-                auto store_c = [&](int row, int col, float v0, float v1, float v2, float v3) {
-                    const int m = m0 + row, n = n0 + col;
-                    const uint32_t off = (m < mlim && n < p.N)
-                                             ? ((uint32_t)(map_row(p, m) - prow0) * (uint32_t)p.ldc + (uint32_t)n) * 2u
-                                             : kOOBRow;
-                    const u32x2 o = {pack_bf16x2(v0, v1), pack_bf16x2(v2, v3)};
-                    // (a per-tile choice would be a branch around each store,
-                    // which the compiler cannot count)
-                    if constexpr (WT)   // sc0 sc1: written through to memory, the copy engines read it
-                        __builtin_amdgcn_raw_buffer_store_b64(o, rC, off, 0, 17);
-                    else
-                        __builtin_amdgcn_raw_buffer_store_b64(o, rC, off, 0, 0);
-                };
-                auto load_p = [&](int blk, char *dst) {
-                    const int mi = blk / FN, ni = blk % FN;
-                    const int n = n0 + wn0 + ni * 32 + 4 * rc;
-#pragma unroll
-                    for (int it = 0; it < 4; ++it) {
-                        const int m = m0 + wm0 + mi * 32 + rr + 8 * it;
-                        const uint32_t off = (m < p.M && n < p.N)
-                                                 ? ((uint32_t)(map_row(p, m) - prow0) * (uint32_t)p.ldp + (uint32_t)n) * 4u
-                                                 : kOOBRow;
-                        __builtin_amdgcn_raw_ptr_buffer_load_lds(rP, LDS_AS(dst + it * 1024), 16, off, 0, 0, 0);
-                    }
-                };
-#pragma unroll
-                for (int blk = 0; blk < AHEAD && blk < NB; ++blk) load_p(blk, pslot[blk]);
-#pragma unroll
-                for (int blk = 0; blk < NB; ++blk) {
-                    char *pcur = pslot[blk % NSLOT];
-                    // into the slot of block blk - 1, whose reads ended the last iteration
-                    if (blk + AHEAD < NB) load_p(blk + AHEAD, pslot[(blk + AHEAD) % NSLOT]);
-                    const int mi = blk / FN, ni = blk % FN;
-#pragma unroll
-                    for (int g = 0; g < 4; ++g) {
-                        const int cc = 2 * g + hi;
-                        f32x4 v4 = {acc[ni][mi][4 * g + 0], acc[ni][mi][4 * g + 1],
-                                    acc[ni][mi][4 * g + 2], acc[ni][mi][4 * g + 3]};
-                        *reinterpret_cast<f32x4 *>(patch + r * 128 + ((cc ^ (r & 7)) << 4)) = v4;
-                    }
-                    __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0): patch written
-#pragma unroll
-                    for (int it = 0; it < 4; ++it) {
-                        const int row = rr + 8 * it;
-                        const f32x4 x = *reinterpret_cast<const f32x4 *>(patch + row * 128 + ((rc ^ (row & 7)) << 4));
-                        const f32x4 pv = *reinterpret_cast<const f32x4 *>(pcur + row * 128 + rc * 16);
-                        store_c(wm0 + mi * 32 + row, wn0 + ni * 32 + 4 * rc, x[0] + pv[0], x[1] + pv[1],
-                                x[2] + pv[2], x[3] + pv[3]);
-                    }
-                    __builtin_amdgcn_s_waitcnt(0xC07F);   // patch and partial read before reuse
+                case 2: finish_split(integral_constant<int, 2>{}, integral_constant<int, 2>{}); break;
+                case 3: finish_split(integral_constant<int, 1>{}, integral_constant<int, 3>{}); break;
+                case 4: finish_split(integral_constant<int, 1>{}, integral_constant<int, 4>{}); break;
+                case 5: finish_split(integral_constant<int, 1>{}, integral_constant<int, 5>{}); break;
+                case 6: finish_split(integral_constant<int, 1>{}, integral_constant<int, 6>{}); break;
+                case 7: finish_split(integral_constant<int, 1>{}, integral_constant<int, 7>{}); break;
+                default: finish_split(integral_constant<int, 1>{}, integral_constant<int, 8>{}); break;
                 }
             } else {
-                through_patch([&](int row, int col, f32x4 x) { store4(row, col, x[0], x[1], x[2], x[3], has_p); });
+                // Each wave turns 32 rows of its accumulators at a time to row
+                // order through a region of the freed stage buffers (FN * 4 KiB
+                // per wave: in A0 / A1 and in W0 / W1 by turns; 16-byte chunk c
+                // of row r at chunk c ^ (r & 7)): written straight from the
+                // accumulation registers, read back 8 consecutive columns per
+                // lane, one 16-byte store of C each, whole rows of the wave's
+                // FN * 32 columns per instruction. The regions are the wave's
+                // own, and a wave's LDS operations run in order, so nothing
+                // waits between the write and the read but the read itself;
+                // the next 32 rows are written while these are stored.
+                constexpr int CPR = 4 * FN;         // 8-column pieces per row
+                constexpr int NIT = 32 * CPR / 64;  // read-back rounds per 32 rows
+                static_assert(FM >= FN, "a region fits two A buffers");
+                char *const region[2] = {smem + wave * FN * 4096, smem + 3 * SA + wave * FN * 4096};
+                const int el = et & 63;
+                auto to_lds = [&](int mi) {
+                    char *w = region[mi & 1] + er * (FN * 128);
+#pragma unroll
+                    for (int ni = 0; ni < FN; ++ni)
+#pragma unroll
+                        for (int g = 0; g < 4; ++g)
+                            *reinterpret_cast<f32x4 *>(w + ni * 128 + (((2 * g + ehi) ^ (er & 7)) << 4)) =
+                                f32x4{acc[ni][mi][4 * g + 0], acc[ni][mi][4 * g + 1], acc[ni][mi][4 * g + 2],
+                                      acc[ni][mi][4 * g + 3]};
+                    asm volatile("" ::: "memory");
+                };
+                // round `it` of rows mi: this lane's row and first column in the tile
+                auto piece_row = [&](int mi, int it) { return wm0 + mi * 32 + (it * 64 + el) / CPR; };
+                auto piece_col = [&](int it) { return wn0 + ((it * 64 + el) % CPR) * 8; };
+                auto from_lds = [&](int mi, int it, float (&x)[8]) {
+                    const int row = (it * 64 + el) / CPR, j = (it * 64 + el) % CPR;
+                    const char *w = region[mi & 1] + row * (FN * 128);
+                    // half of the lanes take their two chunks in the other
+                    // order, so that 8 lanes read 8 different bank groups
+                    const int sw = (j >> 2) & 1;
+                    const f32x4 u = *reinterpret_cast<const f32x4 *>(w + (((2 * j + sw) ^ (row & 7)) << 4));
+                    const f32x4 v = *reinterpret_cast<const f32x4 *>(w + (((2 * j + 1 - sw) ^ (row & 7)) << 4));
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        x[e] = sw ? v[e] : u[e];
+                        x[4 + e] = sw ? u[e] : v[e];
+                    }
+                };
+                if (has_p) {
+                    // The fp32 partial of 32 rows (two 16-byte loads per piece,
+                    // whole lines) is loaded while the rows before it are
+                    // stored. Loads and stores go through buffer resources
+                    // whose bound reads zeros / drops stores for rows or columns
+                    // outside C (or all of a failed tile), so the waits count
+                    // them exactly (no branch between them).
+                    const int prow0 = map_row(p, m0);
+                    const __amdgpu_buffer_rsrc_t rP =
+                        tile_rsrc(pbase, pbytes, (uint64_t)(prow0 - plo) * (uint64_t)p.ldp * 4u);
+                    const __amdgpu_buffer_rsrc_t rC =
+                        tile_rsrc(p.C, p.c_bytes, (uint64_t)prow0 * (uint64_t)p.ldc * 2u);
+                    u32x4 pv[2][NIT][2];
+                    auto load_p = [&](int mi) {
+#pragma unroll
+                        for (int it = 0; it < NIT; ++it) {
+                            const int m = m0 + piece_row(mi, it), n = n0 + piece_col(it);
+                            const uint32_t off = (m < p.M && n < p.N)
+                                                     ? ((uint32_t)(map_row(p, m) - prow0) * (uint32_t)p.ldp + (uint32_t)n) * 4u
+                                                     : kOOBRow;
+                            pv[mi & 1][it][0] = __builtin_amdgcn_raw_buffer_load_b128(rP, off, 0, 0);
+                            pv[mi & 1][it][1] = __builtin_amdgcn_raw_buffer_load_b128(rP, off, 16, 0);
+                        }
+                    };
+                    load_p(0);
+                    to_lds(0);
+#pragma unroll
+                    for (int mi = 0; mi < FM; ++mi) {
+                        if (mi + 1 < FM) {
+                            load_p(mi + 1);
+                            to_lds(mi + 1);
+                        }
+#pragma unroll
+                        for (int it = 0; it < NIT; ++it) {
+                            float x[8];
+                            from_lds(mi, it, x);
+#pragma unroll
+                            for (int e = 0; e < 8; ++e)
+                                x[e] += __builtin_bit_cast(float, (uint32_t)pv[mi & 1][it][e >> 2][e & 3]);
+                            const u32x4 o = {pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3]), pack_bf16x2(x[4], x[5]),
+                                             pack_bf16x2(x[6], x[7])};
+                            const int m = m0 + piece_row(mi, it), n = n0 + piece_col(it);
+                            const uint32_t off = (m < mlim && n < p.N)
+                                                     ? ((uint32_t)(map_row(p, m) - prow0) * (uint32_t)p.ldc + (uint32_t)n) * 2u
+                                                     : kOOBRow;
+                            // sc0 sc1: written through to memory, the copy engines read it
+                            // (a per-tile choice would be a branch around each store)
+                            __builtin_amdgcn_raw_buffer_store_b128(o, rC, off, 0, WT ? 17 : 0);
+                        }
+                    }
+                } else {
+                    to_lds(0);
+#pragma unroll
+                    for (int mi = 0; mi < FM; ++mi) {
+                        if (mi + 1 < FM) to_lds(mi + 1);
+#pragma unroll
+                        for (int it = 0; it < NIT; ++it) {
+                            float x[8];
+                            from_lds(mi, it, x);
+                            const u32x4 o = {pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3]), pack_bf16x2(x[4], x[5]),
+                                             pack_bf16x2(x[6], x[7])};
+                            store8(m0 + piece_row(mi, it), n0 + piece_col(it), o);
+                        }
+                    }
+                }
             }
         }
 
@@ -713,7 +784,7 @@ void gemm_kernel(const GemmParams p) {
             rec[0] = make_uint4((uint32_t)pos, ((uint32_t)rt << 16) | (uint32_t)tn, hw_id(), xcc_id());
             rec[1] = make_uint4(t_tick, t_gate, t_loop, rtc32());
         }
-        pos = s_pos;
+        pos = __builtin_amdgcn_readfirstlane(s_pos);
     }
 
     // exit: the last workgroup out resets the shared counters

@@ -1272,7 +1272,7 @@ static void set_split(GemmParams &g, int cfg) {
     // at most 8 slices: the slice that completes a tile reads every partial,
     // and past 8 that costs more than the finer split gains (InterDecom at
     // d = 16 on the QKV shape: 850 us with up to 16 slices, 756 us with 8)
-    int sp = std::min(std::min(slots / tiles, 8), std::max(1, g.K / kMinSliceK));
+    int sp = std::min(std::min(slots / tiles, kMaxSplit), std::max(1, g.K / kMinSliceK));
     if (sp < 2) return;
     const size_t tile_bytes = (size_t)tile_rows(cfg) * tile_cols(cfg) * sizeof(float);
     while (sp > 1 && (size_t)tiles * sp * tile_bytes > c.split_ws_bytes) --sp;

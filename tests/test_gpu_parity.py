@@ -535,6 +535,24 @@ def test_tile_configs_integer_exact(tile_cfg):
                 assert np.array_equal(host_bits(case.send[q]), rsref[q * rows:(q + 1) * rows])
 
 
+@pytest.mark.parametrize("tile_cfg", [1, 2], indirect=True)
+@pytest.mark.parametrize("K", [8, 64, 72, 128, 136, 192, 256, 328])   # 1 to 6 stages, whole and ragged
+@pytest.mark.parametrize("partial", [False, True])
+def test_stage_counts_integer_exact(tile_cfg, K, partial):
+    # the buffer rotation (three A, two W) from one stage on, tile edges off by one row and 8 columns
+    M, N = 257, 264
+    _say("stage counts", tile_cfg, K, partial)
+    inp = make_int_rs_inputs(M, N, K, 1, seed=K)
+    A, W = dev_bits(inp["A"]), dev_bits(inp["W"])
+    Cm = torch.zeros((M, N), dtype=torch.int16, device="cuda")
+    P = dev_f32(inp["P_in"][0]) if partial else None
+    C.compass_gemm(A, W, Cm, P)
+    torch.cuda.synchronize()
+    pin = inp["P_in"][0].astype(np.float64) if partial else np.zeros((M, N))
+    ref = O.gemm_rs(O.bf16_to_f64(inp["A"]), O.bf16_to_f64(inp["W"]), [pin], 1)
+    assert np.array_equal(host_bits(Cm), O.f64_to_bf16_rne(ref))
+
+
 # ------------------------------------------------------------ per-launch kernel timing
 def test_kernel_times_one_per_launch():
     _say("kernel times")

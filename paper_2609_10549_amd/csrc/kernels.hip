@@ -235,58 +235,50 @@ __device__ __forceinline__ void load_blocks(i32x4 rsrc, uint32_t lds, const uint
     for (int j = 0; j < CNT; ++j) dma16(rsrc, off[j] + kc2, lds + (uint32_t)((j * 4 + wave) * 1024));
 }
 
-// Fragments of MFMA substep kk: 128-byte rows, 16-byte chunk c of row r
-// stored at chunk c ^ swz; fa / fw: this lane's row in the stage's buffers.
-template <int FM, int FN>
-__device__ __forceinline__ void read_frags(const char *fa, const char *fw, int swz, int kk, int hi, bf16x8 (&a)[FM],
-                                           bf16x8 (&b)[FN]) {
-    const int coff = ((2 * kk + hi) ^ swz) << 4;
-#pragma unroll
-    for (int mi = 0; mi < FM; ++mi) a[mi] = *reinterpret_cast<const bf16x8 *>(fa + coff + mi * 32 * 128);
-#pragma unroll
-    for (int ni = 0; ni < FN; ++ni) b[ni] = *reinterpret_cast<const bf16x8 *>(fw + coff + ni * 32 * 128);
+// Fragment `f` of MFMA substep kk in the order the substep needs them (b[0],
+// a[0 .. FM), b[1 .. FN)): 128-byte rows, 16-byte chunk c of row r stored at
+// chunk c ^ swz; fa / fw: this lane's row in the stage's buffers, coff the
+// byte offset of its chunk.
+template <int F, int FM, int FN>
+__device__ __forceinline__ void read_frag(const char *fa, const char *fw, bf16x8 (&a)[FM], bf16x8 (&b)[FN]) {
+    if constexpr (F >= 1 && F <= FM)
+        a[F - 1] = *reinterpret_cast<const bf16x8 *>(fa + (F - 1) * 32 * 128);
+    else
+        b[F == 0 ? 0 : F - FM] = *reinterpret_cast<const bf16x8 *>(fw + (F == 0 ? 0 : F - FM) * 32 * 128);
 }
 
-// MFMAs [I0, I0 + CNT) of a substep (block i: acc[i / FM][i % FM]).
-template <int I0, int CNT, int FM, int FN>
-__device__ __forceinline__ void mfma_range(f32x16 (&acc)[FN][FM], const bf16x8 (&a)[FM], const bf16x8 (&b)[FN]) {
-#pragma unroll
-    for (int i = I0; i < I0 + CNT; ++i)
-        acc[i / FM][i % FM] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[i / FM], a[i % FM], acc[i / FM][i % FM], 0, 0, 0);
+// Where operation `k` of n falls among MFMA slots [lo, hi).
+constexpr int slot_of(int k, int n, int lo, int hi) { return lo + k * (hi - lo) / n; }
+
+// The reads that fall into slot I.
+template <int F, int I, int R0, int R1, int FM, int FN>
+__device__ __forceinline__ void read_slot(const char *fa, const char *fw, bf16x8 (&a)[FM], bf16x8 (&b)[FN]) {
+    if constexpr (F < FM + FN) {
+        if constexpr (slot_of(F, FM + FN, R0, R1) == I) read_frag<F, FM, FN>(fa, fw, a, b);
+        read_slot<F + 1, I, R0, R1, FM, FN>(fa, fw, a, b);
+    }
 }
 
-// MFMAs [I0, I0 + CNT) with the stage loads [0, L) of one operand spread
-// between them, in this order.
-template <int I0, int CNT, int L, int FM, int FN>
-__device__ __forceinline__ void mfma_loads(f32x16 (&acc)[FN][FM], const bf16x8 (&a)[FM], const bf16x8 (&b)[FN],
-                                           i32x4 rsrc, uint32_t lds, const uint32_t *off, uint32_t kc2, int wave) {
+// MFMAs [I0, I1) of a substep on (a, b) (block i: acc[i / FM][i % FM]), with
+// the next substep's fragment reads into (na, nb) spread over MFMA slots
+// [R0, R1) and loads [L0, L0 + LC) of one operand over slots [D0, D1), in
+// exactly this order: an LDS read and a global load each occupy a unit that
+// the four waves share for about one MFMA's time, so a burst of either fills
+// its queue and holds up the MFMAs behind it.
+template <int I, int I1, int R0, int R1, int L0, int LC, int D0, int D1, int FM, int FN>
+__device__ __forceinline__ void mfma_slots(f32x16 (&acc)[FN][FM], const bf16x8 (&a)[FM], const bf16x8 (&b)[FN],
+                                           bf16x8 (&na)[FM], bf16x8 (&nb)[FN], const char *fa, const char *fw,
+                                           i32x4 rsrc, uint32_t lds, const uint32_t *off, uint32_t kc2) {
+    if constexpr (I < I1) {
+        acc[I / FM][I % FM] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[I / FM], a[I % FM], acc[I / FM][I % FM], 0, 0, 0);
+        read_slot<0, I, R0, R1, FM, FN>(fa, fw, na, nb);
 #pragma unroll
-    for (int i = 0; i < CNT; ++i) {
-        const int k = I0 + i;
-        acc[k / FM][k % FM] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[k / FM], a[k % FM], acc[k / FM][k % FM], 0, 0, 0);
-#pragma unroll
-        for (int j = i * L / CNT; j < (i + 1) * L / CNT; ++j)
-            dma16(rsrc, off[j] + kc2, lds + (uint32_t)((j * 4 + wave) * 1024));
+        for (int j = 0; j < LC; ++j)
+            if (slot_of(j, LC, D0, D1) == I) dma16(rsrc, off[L0 + j] + kc2, lds + (uint32_t)((L0 + j) * 4096));
         __builtin_amdgcn_sched_barrier(0);
+        mfma_slots<I + 1, I1, R0, R1, L0, LC, D0, D1, FM, FN>(acc, a, b, na, nb, fa, fw, rsrc, lds, off, kc2);
     }
 }
-
-// Scheduling groups for the CNT MFMAs just emitted: one instruction of class
-// MASK (NX in all) after each MFMA, the rest after the last; then a barrier
-// that nothing is scheduled across.
-template <int CNT, int MASK, int NX>
-__device__ __forceinline__ void interleave() {
-#pragma unroll
-    for (int i = 0; i < CNT - 1; ++i) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        if (i < NX) __builtin_amdgcn_sched_group_barrier(MASK, 1, 0);
-    }
-    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-    if constexpr (NX > CNT - 1) __builtin_amdgcn_sched_group_barrier(MASK, NX - (CNT - 1), 0);
-    __builtin_amdgcn_sched_barrier(0);
-}
-
-constexpr int kDsRead = 0x100;
 
 constexpr int kBK = 64;   // K depth of one LDS stage
 
@@ -422,48 +414,49 @@ void gemm_kernel(const GemmParams p) {
             load_blocks<LA>(rA, aC, offA, kcol(0), wave);
             load_blocks<LW>(rW, wC, offW, kcol(0), wave);
             load_blocks<LA>(rA, aN, offA, kcol(1), wave);
-            load_blocks<LW>(rW, wN, offW, kcol(1), wave);
-            wait_vm_lgkm0<LA + LW>();
+            load_blocks<LW / 2>(rW, wN, offW, kcol(1), wave);
+            wait_vm_lgkm0<LA + LW / 2>();
             lds_barrier();
             bf16x8 a0[FM], b0[FN], a1[FM], b1[FN];
             const char *fa = smem + (wm0 + r) * 128;       // this lane's fragment rows, relative
             const char *fw = smem + (wn0 + r) * 128;       // to a buffer at smem + 0
-            read_frags<FM, FN>(fa + (aC - lds0), fw + (wC - lds0), swz, 0, hi, a0, b0);
-            constexpr int NM = FM * FN, H = NM / 2, ND = FM + FN;
+            int coff[4];
+#pragma unroll
+            for (int kk = 0; kk < 4; ++kk) coff[kk] = ((2 * kk + hi) ^ swz) << 4;
+            {
+                const char *ca = fa + (aC - lds0) + coff[0], *cw = fw + (wC - lds0) + coff[0];
+#pragma unroll
+                for (int mi = 0; mi < FM; ++mi) a0[mi] = *reinterpret_cast<const bf16x8 *>(ca + mi * 32 * 128);
+#pragma unroll
+                for (int ni = 0; ni < FN; ++ni) b0[ni] = *reinterpret_cast<const bf16x8 *>(cw + ni * 32 * 128);
+            }
+            constexpr int NM = FM * FN;
+            constexpr int HA = LA / 2, HW = LW / 2;
+            constexpr int B3 = NM / 8;          // MFMAs of substep 3 before the barrier
+            constexpr int RE = NM - NM / 4;     // substep 2's reads end here, ahead of the barrier's wait
+            const uint32_t wb = (uint32_t)wave * 1024u;
             // Stage st on (aC, wC), its substep-0 fragments in (a0, b0), stage
-            // st + 1 in flight or landed in (aN, wN). Substep 0 issues the A
-            // loads of stage st + 2 into aF, which stage st - 1 freed; substep 3
-            // waits for all of stage st + 1 (the A loads just issued stay in
-            // flight), joins the barrier, reads stage st + 1's first fragments
-            // and issues the W loads of stage st + 2 into wC, whose fragments
+            // st + 1 in flight in (aN, wN). Substep 0 issues the second half of
+            // stage st + 1's W loads, substeps 1 and 2 the A loads of stage
+            // st + 2 into aF, which stage st - 1 freed. Substep 3 waits for all
+            // of stage st + 1 (the A loads just issued stay in flight), joins
+            // the barrier, reads stage st + 1's first fragments and issues the
+            // first half of stage st + 2's W loads into wC, whose fragments
             // every wave has read by then.
             for (int st = 0; st < KT; ++st) {
                 const char *ca = fa + (aC - lds0), *cw = fw + (wC - lds0);
-                const uint32_t kc2 = kcol(st + 2);
-                // substep 0
-                read_frags<FM, FN>(ca, cw, swz, 1, hi, a1, b1);
-                mfma_range<0, H, FM, FN>(acc, a0, b0);
-                interleave<H, kDsRead, ND>();
-                mfma_loads<H, NM - H, LA, FM, FN>(acc, a0, b0, rA, aF, offA, kc2, wave);
-                // substep 1
-                read_frags<FM, FN>(ca, cw, swz, 2, hi, a0, b0);
-                mfma_range<0, H, FM, FN>(acc, a1, b1);
-                interleave<H, kDsRead, ND>();
-                mfma_range<H, NM - H, FM, FN>(acc, a1, b1);
-                __builtin_amdgcn_sched_barrier(0);
-                // substep 2
-                read_frags<FM, FN>(ca, cw, swz, 3, hi, a1, b1);
-                mfma_range<0, H, FM, FN>(acc, a0, b0);
-                interleave<H, kDsRead, ND>();
-                mfma_range<H, NM - H, FM, FN>(acc, a0, b0);
-                __builtin_amdgcn_sched_barrier(0);
-                // substep 3
+                const uint32_t kc1 = kcol(st + 1), kc2 = kcol(st + 2);
+                mfma_slots<0, NM, 0, NM, HW, LW - HW, 0, NM, FM, FN>(acc, a0, b0, a1, b1, ca + coff[1], cw + coff[1], rW,
+                                                                   wN + wb, offW, kc1);
+                mfma_slots<0, NM, 0, NM, 0, HA, 0, NM, FM, FN>(acc, a1, b1, a0, b0, ca + coff[2], cw + coff[2], rA,
+                                                             aF + wb, offA, kc2);
+                mfma_slots<0, NM, 0, RE, HA, LA - HA, 0, NM, FM, FN>(acc, a0, b0, a1, b1, ca + coff[3], cw + coff[3], rA,
+                                                                  aF + wb, offA, kc2);
+                const char *na = fa + (aN - lds0) + coff[0], *nw = fw + (wN - lds0) + coff[0];
+                mfma_slots<0, B3, NM, NM + 1, 0, 0, 0, 1, FM, FN>(acc, a1, b1, a0, b0, na, nw, rW, 0u, offW, 0u);
                 wait_vm_lgkm0<LA>();
                 lds_barrier();
-                read_frags<FM, FN>(fa + (aN - lds0), fw + (wN - lds0), swz, 0, hi, a0, b0);
-                mfma_range<0, H, FM, FN>(acc, a1, b1);
-                interleave<H, kDsRead, ND>();
-                mfma_loads<H, NM - H, LW, FM, FN>(acc, a1, b1, rW, wC, offW, kc2, wave);
+                mfma_slots<B3, NM, B3, NM, 0, HW, B3, NM, FM, FN>(acc, a1, b1, a0, b0, na, nw, rW, wC + wb, offW, kc2);
                 const uint32_t t = aC;
                 aC = aN; aN = aF; aF = t;
                 const uint32_t u = wC;

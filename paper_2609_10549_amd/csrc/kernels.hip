@@ -1,7 +1,7 @@
 // gfx950 kernels of the Compass hot path.
 //
 // gemm_kernel<BM, BN, RS, WT>: persistent bf16 GEMM, C = A * W^T with fp32
-// accumulation on the CDNA4 matrix cores (v_mfma_f32_32x32x16_bf16) and one
+// accumulation on the CDNA4 matrix cores (v_mfma_f32_16x16x32_bf16) and one
 // bf16 round-to-nearest-even store. Workgroups take BM x BN output tiles from
 // atomic ticket queues in the order the host chose (ring-arrival order for
 // TA-IntraFusion, Section III-B), and, depending on the gate mode, wait on the
@@ -16,19 +16,27 @@
 // in that XCD's L2.
 //
 // Data path per tile: 4 waves split the tile 2 x 2; each wave holds
-// (BM/2) x (BN/2) fp32 accumulators as 32 x 32 MFMA blocks. A and W stream
-// through two LDS stages of K = 64 (rows of 128 bytes, whole cache lines per
-// load: the texture path's cost grows with the lines a load touches) with
+// (BM/2) x (BN/2) fp32 accumulators as 16 x 16 MFMA blocks. A and W stream
+// through LDS in stages of K = 64 (rows of 128 bytes, whole cache lines per
+// load: the texture path's cost grows with the lines a load touches), three
+// buffers of A and two of W (all 160 KiB for a 256 x 256 tile), with
 // buffer_load ... lds (no register staging; out-of-range rows or K columns
-// read as zero through the buffer bound). The one barrier per stage sits
-// before its last substep: by then every wave has read that stage's
-// fragments, so the next-but-one stage's loads may overwrite it, and the next
-// stage's first fragments are read while the last substep computes. Loads of
-// stage s + 1 go out in the last substep of stage s - 1 (A) and the first of
-// stage s (W). Fragment reads of the next substep are issued between the
-// current one's MFMAs; scheduling barriers keep the compiler from sinking
-// them to their use. The 16-byte chunks of LDS row r are XOR-permuted with
-// (r >> 1) & 7, so a 32-row fragment read hits distinct banks.
+// read as zero through the buffer bound). The 16-byte chunks of LDS row r are
+// XOR-permuted with (r >> 1) & 7, so a fragment read hits distinct banks.
+//
+// What bounds it: the matrix cores at the clock the chip's power allows
+// (1.4 - 1.55 GHz under this load, 2.4 GHz nominal), so what counts is cycles
+// lost to waits and energy per flop. 8192 x 6144 x 12288, 256 x 256 tiles,
+// each step against the one before it on one box:
+//  - three A buffers in place of two (loads have 1 to 1.75 stages to land; one
+//    barrier per stage): 942 -> 925 us;
+//  - LDS reads and global loads one at a time between the MFMAs in place of
+//    bursts of eight, which filled their queues and held up the MFMAs behind
+//    them (matrix cores 75 -> 80 % busy): 925 -> 908 us;
+//  - v_mfma_f32_16x16x32_bf16 in place of 32x32x16: half the accumulator
+//    traffic per flop (each accumulator is read and written once per 32 of K
+//    in place of 16), a higher clock and shorter stalls: 908 -> 834 us
+//    (1.48 PFLOP/s; stage time 1.46 -> 1.38 us).
 //
 // join_kernel: one wave that (optionally) marks the start of a transfer job
 // and waits for a list of flags, putting the end of the copy side onto the
@@ -235,16 +243,15 @@ __device__ __forceinline__ void load_blocks(i32x4 rsrc, uint32_t lds, const uint
     for (int j = 0; j < CNT; ++j) dma16(rsrc, off[j] + kc2, lds + (uint32_t)((j * 4 + wave) * 1024));
 }
 
-// Fragment `f` of MFMA substep kk in the order the substep needs them (b[0],
-// a[0 .. FM), b[1 .. FN)): 128-byte rows, 16-byte chunk c of row r stored at
-// chunk c ^ swz; fa / fw: this lane's row in the stage's buffers, coff the
-// byte offset of its chunk.
+// Fragment F of an MFMA substep in the order the substep needs them (b[0],
+// a[0 .. FM), b[1 .. FN)): 16 rows of 128 bytes each; fa / fw: this lane's
+// row and 16-byte chunk in the stage's buffers.
 template <int F, int FM, int FN>
 __device__ __forceinline__ void read_frag(const char *fa, const char *fw, bf16x8 (&a)[FM], bf16x8 (&b)[FN]) {
     if constexpr (F >= 1 && F <= FM)
-        a[F - 1] = *reinterpret_cast<const bf16x8 *>(fa + (F - 1) * 32 * 128);
+        a[F - 1] = *reinterpret_cast<const bf16x8 *>(fa + (F - 1) * 16 * 128);
     else
-        b[F == 0 ? 0 : F - FM] = *reinterpret_cast<const bf16x8 *>(fw + (F == 0 ? 0 : F - FM) * 32 * 128);
+        b[F == 0 ? 0 : F - FM] = *reinterpret_cast<const bf16x8 *>(fw + (F == 0 ? 0 : F - FM) * 16 * 128);
 }
 
 // Where operation `k` of n falls among MFMA slots [lo, hi).
@@ -266,11 +273,11 @@ __device__ __forceinline__ void read_slot(const char *fa, const char *fw, bf16x8
 // the four waves share for about one MFMA's time, so a burst of either fills
 // its queue and holds up the MFMAs behind it.
 template <int I, int I1, int R0, int R1, int L0, int LC, int D0, int D1, int FM, int FN>
-__device__ __forceinline__ void mfma_slots(f32x16 (&acc)[FN][FM], const bf16x8 (&a)[FM], const bf16x8 (&b)[FN],
+__device__ __forceinline__ void mfma_slots(f32x4 (&acc)[FN][FM], const bf16x8 (&a)[FM], const bf16x8 (&b)[FN],
                                            bf16x8 (&na)[FM], bf16x8 (&nb)[FN], const char *fa, const char *fw,
                                            i32x4 rsrc, uint32_t lds, const uint32_t *off, uint32_t kc2) {
     if constexpr (I < I1) {
-        acc[I / FM][I % FM] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[I / FM], a[I % FM], acc[I / FM][I % FM], 0, 0, 0);
+        acc[I / FM][I % FM] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[I / FM], a[I % FM], acc[I / FM][I % FM], 0, 0, 0);
         read_slot<0, I, R0, R1, FM, FN>(fa, fw, na, nb);
 #pragma unroll
         for (int j = 0; j < LC; ++j)
@@ -290,7 +297,7 @@ template <int BM, int BN, bool RS, bool WT = false>
 __global__ __launch_bounds__(kThreads, BM == 256 ? 1 : 2)
 void gemm_kernel(const GemmParams p) {
     constexpr int WM = BM / 2, WN = BN / 2;
-    constexpr int FM = WM / 32, FN = WN / 32;
+    constexpr int FM = WM / 16, FN = WN / 16;
     constexpr int LA = BM / 32, LW = BN / 32;   // loads per wave and stage of A, W
     constexpr int SA = BM * 128, SW = BN * 128; // bytes of one stage buffer
     static_assert(SA >= 16384 && SW >= 16384, "stage buffers hold the epilogue's partial blocks");
@@ -317,8 +324,8 @@ void gemm_kernel(const GemmParams p) {
     // that the permutation (row >> 1) & 7 puts at its physical chunk lane & 7
     const int lrow0 = 8 * wave + (lane >> 3);
     const int cchunk = (lane & 7) ^ ((4 * wave + (lane >> 4)) & 7);
-    const int r = lane & 31;                       // fragment row
-    const int hi = lane >> 5;                      // fragment K half
+    const int r = lane & 15;                       // fragment row
+    const int kq = lane >> 4;                      // fragment K quarter
     const int swz = (r >> 1) & 7;
 
     uint64_t known = 0;   // partitions already acquired by this workgroup
@@ -372,13 +379,13 @@ void gemm_kernel(const GemmParams p) {
         }
         if (!RS && traced && tid == 0) t_gate = rtc32();
 
-        f32x16 acc[FN][FM];
+        f32x4 acc[FN][FM];
 #pragma unroll
         for (int ni = 0; ni < FN; ++ni)
 #pragma unroll
             for (int mi = 0; mi < FM; ++mi)
 #pragma unroll
-                for (int e = 0; e < 16; ++e) acc[ni][mi][e] = 0.0f;
+                for (int e = 0; e < 4; ++e) acc[ni][mi][e] = 0.0f;
 
         {   // a timed-out tile still runs (its loads stay in bounds); only its
             // stores are dropped
@@ -414,49 +421,42 @@ void gemm_kernel(const GemmParams p) {
             load_blocks<LA>(rA, aC, offA, kcol(0), wave);
             load_blocks<LW>(rW, wC, offW, kcol(0), wave);
             load_blocks<LA>(rA, aN, offA, kcol(1), wave);
-            load_blocks<LW / 2>(rW, wN, offW, kcol(1), wave);
-            wait_vm_lgkm0<LA + LW / 2>();
+            load_blocks<LW>(rW, wN, offW, kcol(1), wave);
+            wait_vm_lgkm0<LA + LW>();
             lds_barrier();
             bf16x8 a0[FM], b0[FN], a1[FM], b1[FN];
             const char *fa = smem + (wm0 + r) * 128;       // this lane's fragment rows, relative
             const char *fw = smem + (wn0 + r) * 128;       // to a buffer at smem + 0
-            int coff[4];
-#pragma unroll
-            for (int kk = 0; kk < 4; ++kk) coff[kk] = ((2 * kk + hi) ^ swz) << 4;
+            const int coff0 = (kq ^ swz) << 4, coff1 = ((4 + kq) ^ swz) << 4;
             {
-                const char *ca = fa + (aC - lds0) + coff[0], *cw = fw + (wC - lds0) + coff[0];
+                const char *ca = fa + (aC - lds0) + coff0, *cw = fw + (wC - lds0) + coff0;
 #pragma unroll
-                for (int mi = 0; mi < FM; ++mi) a0[mi] = *reinterpret_cast<const bf16x8 *>(ca + mi * 32 * 128);
+                for (int mi = 0; mi < FM; ++mi) a0[mi] = *reinterpret_cast<const bf16x8 *>(ca + mi * 16 * 128);
 #pragma unroll
-                for (int ni = 0; ni < FN; ++ni) b0[ni] = *reinterpret_cast<const bf16x8 *>(cw + ni * 32 * 128);
+                for (int ni = 0; ni < FN; ++ni) b0[ni] = *reinterpret_cast<const bf16x8 *>(cw + ni * 16 * 128);
             }
             constexpr int NM = FM * FN;
-            constexpr int HA = LA / 2, HW = LW / 2;
-            constexpr int B3 = NM / 8;          // MFMAs of substep 3 before the barrier
-            constexpr int RE = NM - NM / 4;     // substep 2's reads end here, ahead of the barrier's wait
+            constexpr int RE = NM - NM / 4;     // substep 0's reads end here, ahead of the barrier's wait
+            constexpr int B1 = NM / 16;         // MFMAs of substep 1 before the barrier
             const uint32_t wb = (uint32_t)wave * 1024u;
             // Stage st on (aC, wC), its substep-0 fragments in (a0, b0), stage
-            // st + 1 in flight in (aN, wN). Substep 0 issues the second half of
-            // stage st + 1's W loads, substeps 1 and 2 the A loads of stage
-            // st + 2 into aF, which stage st - 1 freed. Substep 3 waits for all
-            // of stage st + 1 (the A loads just issued stay in flight), joins
-            // the barrier, reads stage st + 1's first fragments and issues the
-            // first half of stage st + 2's W loads into wC, whose fragments
-            // every wave has read by then.
+            // st + 1 in flight in (aN, wN). Substep 0 (the first 32 of K) reads
+            // substep 1's fragments and issues the A loads of stage st + 2 into
+            // aF, which stage st - 1 freed. Substep 1 waits for all of stage
+            // st + 1 (the A loads just issued stay in flight), joins the
+            // barrier, reads stage st + 1's first fragments and issues stage
+            // st + 2's W loads into wC, whose fragments every wave has read.
             for (int st = 0; st < KT; ++st) {
                 const char *ca = fa + (aC - lds0), *cw = fw + (wC - lds0);
-                const uint32_t kc1 = kcol(st + 1), kc2 = kcol(st + 2);
-                mfma_slots<0, NM, 0, NM, HW, LW - HW, 0, NM, FM, FN>(acc, a0, b0, a1, b1, ca + coff[1], cw + coff[1], rW,
-                                                                   wN + wb, offW, kc1);
-                mfma_slots<0, NM, 0, NM, 0, HA, 0, NM, FM, FN>(acc, a1, b1, a0, b0, ca + coff[2], cw + coff[2], rA,
-                                                             aF + wb, offA, kc2);
-                mfma_slots<0, NM, 0, RE, HA, LA - HA, 0, NM, FM, FN>(acc, a0, b0, a1, b1, ca + coff[3], cw + coff[3], rA,
-                                                                  aF + wb, offA, kc2);
-                const char *na = fa + (aN - lds0) + coff[0], *nw = fw + (wN - lds0) + coff[0];
-                mfma_slots<0, B3, NM, NM + 1, 0, 0, 0, 1, FM, FN>(acc, a1, b1, a0, b0, na, nw, rW, 0u, offW, 0u);
+                const uint32_t kc2 = kcol(st + 2);
+                mfma_slots<0, NM, 0, RE, 0, LA, 0, NM, FM, FN>(acc, a0, b0, a1, b1, ca + coff1, cw + coff1, rA, aF + wb,
+                                                             offA, kc2);
+                const char *na = fa + (aN - lds0) + coff0, *nw = fw + (wN - lds0) + coff0;
+                mfma_slots<0, B1, NM, NM + 1, 0, 0, 0, 1, FM, FN>(acc, a1, b1, a0, b0, na, nw, rW, 0u, offW, 0u);
                 wait_vm_lgkm0<LA>();
                 lds_barrier();
-                mfma_slots<B3, NM, B3, NM, 0, HW, B3, NM, FM, FN>(acc, a1, b1, a0, b0, na, nw, rW, wC + wb, offW, kc2);
+                mfma_slots<B1, NM, B1, NM, 0, LW, B1, B1 + (NM - B1) * 3 / 4, FM, FN>(acc, a1, b1, a0, b0, na, nw, rW,
+                                                                                    wC + wb, offW, kc2);
                 const uint32_t t = aC;
                 aC = aN; aN = aF; aF = t;
                 const uint32_t u = wC;
@@ -480,7 +480,7 @@ void gemm_kernel(const GemmParams p) {
         // not kept (spilled) over the main loop
         int et = tid;
         asm volatile("" : "+v"(et));
-        const int er = et & 31, ehi = (et >> 5) & 1;
+        const int er = et & 15, eq = (et >> 4) & 3;
         const int mlim = failed ? 0 : p.M;   // a failed tile stores nothing
         // the tile's partial sum: from P, or, for the rows of an aliased
         // range (a whole number of tiles), from that range's own buffer
@@ -515,21 +515,15 @@ void gemm_kernel(const GemmParams p) {
                 }
             }
         };
-        // Of a 32 x 32 block in the accumulators' layout, lane (r, hi) holds
-        // row r, columns 8 g + 4 hi + 0..3 as values 4 g + 0..3. Exchanging the
-        // packed pairs of groups 2 j and 2 j + 1 between the two halves of the
-        // wave leaves each lane 8 consecutive columns, 16 j + 8 hi.
-        auto store_block = [&](int mi, int ni, const float (&x)[16]) {
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const float *y = x + 8 * j;
-                const u32x2 s0 =
-                    __builtin_amdgcn_permlane32_swap(pack_bf16x2(y[0], y[1]), pack_bf16x2(y[4], y[5]), false, false);
-                const u32x2 s1 =
-                    __builtin_amdgcn_permlane32_swap(pack_bf16x2(y[2], y[3]), pack_bf16x2(y[6], y[7]), false, false);
-                store8(m0 + wm0 + mi * 32 + er, n0 + wn0 + ni * 32 + 16 * j + 8 * ehi,
-                       u32x4{s0[0], s1[0], s0[1], s1[1]});
-            }
+        // Of a 16 x 16 block in the accumulators' layout, lane (r, q) holds row
+        // r, columns 4 q + 0..3. Exchanging the packed values of blocks ni and
+        // ni + 1 between the 16-lane rows of the wave leaves each lane 8
+        // consecutive columns, those from 8 (q / 2) of block ni + q % 2.
+        auto store_pair = [&](int mi, int ni, f32x4 x, f32x4 y) {
+            const u32x2 s0 = __builtin_amdgcn_permlane16_swap(pack_bf16x2(x[0], x[1]), pack_bf16x2(y[0], y[1]), false, false);
+            const u32x2 s1 = __builtin_amdgcn_permlane16_swap(pack_bf16x2(x[2], x[3]), pack_bf16x2(y[2], y[3]), false, false);
+            store8(m0 + wm0 + mi * 16 + er, n0 + wn0 + (ni + (eq & 1)) * 16 + 8 * (eq >> 1),
+                   u32x4{s0[0], s1[0], s0[1], s1[1]});
         };
         const bool has_p = RS && p.P != nullptr;
 
@@ -544,12 +538,7 @@ void gemm_kernel(const GemmParams p) {
 #pragma unroll
             for (int ni = 0; ni < FN; ++ni)
 #pragma unroll
-                for (int mi = 0; mi < FM; ++mi)
-#pragma unroll
-                    for (int g = 0; g < 4; ++g)
-                        ws[((ni * FM + mi) * 4 + g) * kThreads] =
-                            f32x4{acc[ni][mi][4 * g + 0], acc[ni][mi][4 * g + 1], acc[ni][mi][4 * g + 2],
-                                  acc[ni][mi][4 * g + 3]};
+                for (int mi = 0; mi < FM; ++mi) ws[(ni * FM + mi) * kThreads] = acc[ni][mi];
             // The workspace is uncached device memory: a store acknowledged
             // to the wave is in memory, visible to every XCD, and loads read
             // memory. So ordering needs no cache maintenance: each wave waits
@@ -581,52 +570,49 @@ void gemm_kernel(const GemmParams p) {
         if (finish) {
             if (split) {
                 const f32x4 *ws0 = reinterpret_cast<const f32x4 *>(p.split_ws + (size_t)wsf * (BM * BN)) + et;
-                // B 32 x 32 blocks at a time, all their slices' loads (and the
+                // B pairs of blocks at a time, all their slices' loads (and the
                 // partial sum's) in flight at once, then each summed in slice
                 // order: the workspace is uncached, so every load costs a memory
-                // round trip, and 4 B S of them overlap. With the slice count a
-                // compile-time constant (EX) the loads carry no branch, and the
-                // waits before the sums count them exactly; otherwise S is an
-                // upper bound and slices from ns on are skipped.
+                // round trip, and 2 B S of them overlap. The slice count is a
+                // compile-time constant: the loads carry no branch, and the
+                // waits before the sums count them exactly.
                 auto finish_split = [&](auto b_const, auto s_const) {
                     constexpr int B = decltype(b_const)::value, S = decltype(s_const)::value;
-                    static_assert((FM * FN) % B == 0, "whole batches");
+                    constexpr int NP = FM * FN / 2;   // pairs (mi, 2 nj), (mi, 2 nj + 1)
+                    static_assert(NP % B == 0, "whole batches");
 #pragma unroll 1
-                    for (int blk0 = 0; blk0 < FM * FN; blk0 += B) {
-                        f32x4 part[B][4][S];
-                        f32x4 pv[B][4];
+                    for (int u0 = 0; u0 < NP; u0 += B) {
+                        f32x4 part[B][2][S];
+                        f32x4 pv[B][2];
 #pragma unroll
                         for (int b = 0; b < B; ++b) {
-                            const int blk = blk0 + b, ni = blk / FM, mi = blk % FM;
+                            const int mi = (u0 + b) % FM, nj = (u0 + b) / FM;
+                            const int m = m0 + wm0 + mi * 16 + er;
 #pragma unroll
-                            for (int g = 0; g < 4; ++g)
+                            for (int h = 0; h < 2; ++h) {
+                                const int ni = 2 * nj + h;
 #pragma unroll
                                 for (int jj = 0; jj < S; ++jj)
-                                    part[b][g][jj] = ws0[(size_t)jj * (BM * BN / 4) + (blk * 4 + g) * kThreads];
-                            const int m = m0 + wm0 + mi * 32 + er;
-#pragma unroll
-                            for (int g = 0; g < 4; ++g) {
-                                const int n = n0 + wn0 + ni * 32 + 8 * g + 4 * ehi;
-                                pv[b][g] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+                                    part[b][h][jj] = ws0[(size_t)jj * (BM * BN / 4) + (ni * FM + mi) * kThreads];
+                                const int n = n0 + wn0 + ni * 16 + 4 * eq;
+                                pv[b][h] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
                                 if (has_p && m < p.M && n < p.N)
-                                    pv[b][g] = *reinterpret_cast<const f32x4 *>(
+                                    pv[b][h] = *reinterpret_cast<const f32x4 *>(
                                         pbase + (size_t)(map_row(p, m) - plo) * p.ldp + n);
                             }
                         }
 #pragma unroll
                         for (int b = 0; b < B; ++b) {
-                            const int blk = blk0 + b, ni = blk / FM, mi = blk % FM;
-                            float x[16];
+                            const int mi = (u0 + b) % FM, nj = (u0 + b) / FM;
+                            f32x4 x[2];
 #pragma unroll
-                            for (int g = 0; g < 4; ++g) {
-                                f32x4 sum = part[b][g][0];
+                            for (int h = 0; h < 2; ++h) {
+                                x[h] = part[b][h][0];
 #pragma unroll
-                                for (int jj = 1; jj < S; ++jj)
-                                    sum += part[b][g][jj];
-#pragma unroll
-                                for (int e = 0; e < 4; ++e) x[4 * g + e] = sum[e] + pv[b][g][e];
+                                for (int jj = 1; jj < S; ++jj) x[h] += part[b][h][jj];
+                                x[h] += pv[b][h];
                             }
-                            store_block(mi, ni, x);
+                            store_pair(mi, 2 * nj, x[0], x[1]);
                         }
                     }
                 };
@@ -636,39 +622,39 @@ void gemm_kernel(const GemmParams p) {
                 // leaves.
                 using std::integral_constant;
                 switch (ns) {
-                case 2: finish_split(integral_constant<int, 2>{}, integral_constant<int, 2>{}); break;
-                case 3: finish_split(integral_constant<int, 1>{}, integral_constant<int, 3>{}); break;
-                case 4: finish_split(integral_constant<int, 1>{}, integral_constant<int, 4>{}); break;
-                case 5: finish_split(integral_constant<int, 1>{}, integral_constant<int, 5>{}); break;
-                case 6: finish_split(integral_constant<int, 1>{}, integral_constant<int, 6>{}); break;
-                case 7: finish_split(integral_constant<int, 1>{}, integral_constant<int, 7>{}); break;
-                default: finish_split(integral_constant<int, 1>{}, integral_constant<int, 8>{}); break;
+                case 2: finish_split(integral_constant<int, 4>{}, integral_constant<int, 2>{}); break;
+                case 3: finish_split(integral_constant<int, 2>{}, integral_constant<int, 3>{}); break;
+                case 4: finish_split(integral_constant<int, 2>{}, integral_constant<int, 4>{}); break;
+                case 5: finish_split(integral_constant<int, 2>{}, integral_constant<int, 5>{}); break;
+                case 6: finish_split(integral_constant<int, 2>{}, integral_constant<int, 6>{}); break;
+                case 7: finish_split(integral_constant<int, 2>{}, integral_constant<int, 7>{}); break;
+                default: finish_split(integral_constant<int, 2>{}, integral_constant<int, 8>{}); break;
                 }
             } else {
                 // Each wave turns 32 rows of its accumulators at a time to row
-                // order through a region of the freed stage buffers (FN * 4 KiB
+                // order through a region of the freed stage buffers (FN * 2 KiB
                 // per wave: in A0 / A1 and in W0 / W1 by turns; 16-byte chunk c
                 // of row r at chunk c ^ (r & 7)): written straight from the
                 // accumulation registers, read back 8 consecutive columns per
                 // lane, one 16-byte store of C each, whole rows of the wave's
-                // FN * 32 columns per instruction. The regions are the wave's
+                // FN * 16 columns per instruction. The regions are the wave's
                 // own, and a wave's LDS operations run in order, so nothing
                 // waits between the write and the read but the read itself;
                 // the next 32 rows are written while these are stored.
-                constexpr int CPR = 4 * FN;         // 8-column pieces per row
+                constexpr int CPR = 2 * FN;         // 8-column pieces per row
                 constexpr int NIT = 32 * CPR / 64;  // read-back rounds per 32 rows
+                constexpr int RB = FN * 64;         // bytes of one row in the region
                 static_assert(FM >= FN, "a region fits two A buffers");
-                char *const region[2] = {smem + wave * FN * 4096, smem + 3 * SA + wave * FN * 4096};
+                char *const region[2] = {smem + wave * 32 * RB, smem + 3 * SA + wave * 32 * RB};
                 const int el = et & 63;
                 auto to_lds = [&](int mi) {
-                    char *w = region[mi & 1] + er * (FN * 128);
+                    char *w = region[mi & 1] + er * RB;
 #pragma unroll
-                    for (int ni = 0; ni < FN; ++ni)
+                    for (int h = 0; h < 2; ++h)
 #pragma unroll
-                        for (int g = 0; g < 4; ++g)
-                            *reinterpret_cast<f32x4 *>(w + ni * 128 + (((2 * g + ehi) ^ (er & 7)) << 4)) =
-                                f32x4{acc[ni][mi][4 * g + 0], acc[ni][mi][4 * g + 1], acc[ni][mi][4 * g + 2],
-                                      acc[ni][mi][4 * g + 3]};
+                        for (int ni = 0; ni < FN; ++ni)
+                            *reinterpret_cast<f32x4 *>(w + h * 16 * RB + (((4 * ni + eq) ^ (er & 7)) << 4)) =
+                                acc[ni][2 * mi + h];
                     asm volatile("" ::: "memory");
                 };
                 // round `it` of rows mi: this lane's row and first column in the tile
@@ -676,7 +662,7 @@ void gemm_kernel(const GemmParams p) {
                 auto piece_col = [&](int it) { return wn0 + ((it * 64 + el) % CPR) * 8; };
                 auto from_lds = [&](int mi, int it, float (&x)[8]) {
                     const int row = (it * 64 + el) / CPR, j = (it * 64 + el) % CPR;
-                    const char *w = region[mi & 1] + row * (FN * 128);
+                    const char *w = region[mi & 1] + row * RB;
                     // half of the lanes take their two chunks in the other
                     // order, so that 8 lanes read 8 different bank groups
                     const int sw = (j >> 2) & 1;
@@ -715,8 +701,8 @@ void gemm_kernel(const GemmParams p) {
                     load_p(0);
                     to_lds(0);
 #pragma unroll
-                    for (int mi = 0; mi < FM; ++mi) {
-                        if (mi + 1 < FM) {
+                    for (int mi = 0; mi < FM / 2; ++mi) {
+                        if (mi + 1 < FM / 2) {
                             load_p(mi + 1);
                             to_lds(mi + 1);
                         }
@@ -741,8 +727,8 @@ void gemm_kernel(const GemmParams p) {
                 } else {
                     to_lds(0);
 #pragma unroll
-                    for (int mi = 0; mi < FM; ++mi) {
-                        if (mi + 1 < FM) to_lds(mi + 1);
+                    for (int mi = 0; mi < FM / 2; ++mi) {
+                        if (mi + 1 < FM / 2) to_lds(mi + 1);
 #pragma unroll
                         for (int it = 0; it < NIT; ++it) {
                             float x[8];

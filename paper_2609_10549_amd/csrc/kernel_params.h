@@ -19,14 +19,26 @@ constexpr int kMaxSplitTiles = 512;  // tiles of a split-K launch (one counter e
 constexpr int kMaxSplit = 8;         // K slices per tile (the finisher has an instance per count)
 constexpr uint64_t kTileSpanMax = 1ull << 30;   // bytes of A, W or P one tile may span
 
-// Tile configurations of the GEMM kernel.
+// Tile configurations of the GEMM kernel: rows x columns of the output tile
+// and the workgroups a CU holds. LDS (160 KiB per CU): DW W and DW + 1 A stage
+// buffers of 128 bytes per row or column.
 enum TileCfg : int {
-    kTile256 = 0,   // 256 x 256 output tile, 160 KiB LDS, one workgroup per CU
-    kTile128 = 1,   // 128 x 128 output tile, 80 KiB LDS, two workgroups per CU
+    kTile256 = 0,        // 256 x 256, DW 2, 160 KiB
+    kTile128 = 1,        // 128 x 128, DW 2,  80 KiB
+    kTile256x192 = 2,    // 256 x 192, DW 2, 144 KiB
+    kTile256x128 = 3,    // 256 x 128, DW 2, 128 KiB
+    kTile128Deep = 4,    // 128 x 128, DW 4, 144 KiB
+    kTile128x64 = 5,     // 128 x 64,  DW 2,  64 KiB
+    kTile128x64Deep = 6, // 128 x 64,  DW 4, 112 KiB
+    kTile64 = 7,         //  64 x 64,  DW 4,  72 KiB
+    kTileCfgs = 8,
 };
-inline int tile_rows(int cfg) { return cfg == kTile256 ? 256 : 128; }
-inline int tile_cols(int cfg) { return cfg == kTile256 ? 256 : 128; }
-inline int tile_wg_per_cu(int cfg) { return cfg == kTile256 ? 1 : 2; }
+struct TileShape { int rows, cols, wg_per_cu; };
+constexpr TileShape kTileShapes[kTileCfgs] = {{256, 256, 1}, {128, 128, 2}, {256, 192, 1}, {256, 128, 1},
+                                              {128, 128, 1}, {128, 64, 2},  {128, 64, 1},  {64, 64, 2}};
+inline int tile_rows(int cfg) { return kTileShapes[cfg].rows; }
+inline int tile_cols(int cfg) { return kTileShapes[cfg].cols; }
+inline int tile_wg_per_cu(int cfg) { return kTileShapes[cfg].wg_per_cu; }
 
 // Where a tile waits for its partitions' arrival flags.
 enum GateMode : int {
@@ -65,6 +77,10 @@ struct GemmParams {
     // positions walk group_m row tiles before the next column tile
     int nq, q_size, group_m;
     int grid;
+    // 1: no tickets. Workgroup b takes work position static_position(b, j) in
+    // its round j (a launch whose tiles wait for nothing finishes them in step,
+    // and the next position is known without an atomic round trip)
+    int fixed;
     // first-ticket spreading: the second workgroup on a CU (by HW_ID) takes
     // its first ticket only once `spread_wait` tickets of its queue are gone
     // (or after ~10 us), so the first tickets land one per CU; 0 = off.
@@ -136,6 +152,20 @@ struct JoinParams {
 __host__ __device__ inline int work_items(const GemmParams &p) {
     const int tiles = p.tiles_m * p.tiles_n;
     return p.head_tiles * p.head_split + (p.split_from - p.head_tiles) + (tiles - p.split_from) * p.ksplit;
+}
+
+// Work position of workgroup b in its round j (`fixed` launches), or -1 when
+// the round has none for it. A round deals the next grid positions, or those
+// that are left, to the XCDs (b % 8) in consecutive runs of equal length, give
+// or take one, so that the tiles an XCD holds at a time share rows and columns.
+__host__ __device__ inline int static_position(const GemmParams &p, int b, int j) {
+    const int first = j * p.grid, all = work_items(p);
+    const int left = all - first < p.grid ? all - first : p.grid;
+    if (left <= 0) return -1;
+    const int v = b % kMaxQueues, c = b / kMaxQueues;
+    const int q = left / kMaxQueues, rem = left % kMaxQueues;
+    if (c >= q + (v < rem ? 1 : 0)) return -1;
+    return first + v * q + (v < rem ? v : rem) + c;
 }
 
 // One work item: the tile at position `tpos` of the ready order and, when

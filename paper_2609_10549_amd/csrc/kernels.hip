@@ -293,22 +293,26 @@ constexpr int kBK = 64;   // K depth of one LDS stage
 // RS = true: optional epilogue gate, fp32 partial add, chunk-done signalling;
 // WT = true (a launch whose finished chunks the copy engines send on): the
 // partial-add epilogue stores every tile with system-scope write-through.
-template <int BM, int BN, bool RS, bool WT = false>
-__global__ __launch_bounds__(kThreads, BM == 256 ? 1 : 2)
+// DW: W stage buffers (DW + 1 of A). The loads of a stage go out DW - 1 to DW
+// stages before their use.
+template <int BM, int BN, int DW, bool RS, bool WT = false>
+__global__ __launch_bounds__(kThreads, (160 << 10) / (((DW + 1) * BM + DW * BN) * 128))
 void gemm_kernel(const GemmParams p) {
     constexpr int WM = BM / 2, WN = BN / 2;
     constexpr int FM = WM / 16, FN = WN / 16;
     constexpr int LA = BM / 32, LW = BN / 32;   // loads per wave and stage of A, W
     constexpr int SA = BM * 128, SW = BN * 128; // bytes of one stage buffer
-    static_assert(SA >= 16384 && SW >= 16384, "stage buffers hold the epilogue's partial blocks");
-    // three A buffers, then two W buffers
-    __shared__ __attribute__((aligned(1024))) char smem[3 * SA + 2 * SW];
-    // control words in the tail of the third A buffer: the first load that
+    constexpr bool kSplits = BM > 64;           // (the host never splits K of the smallest tile)
+    constexpr int NA = DW + 1;
+    constexpr bool kAcc = NA * SA + DW * SW > (80 << 10);   // one workgroup per CU
+    // the A buffers, then the W buffers
+    __shared__ __attribute__((aligned(1024))) char smem[NA * SA + DW * SW];
+    // control words in the tail of the last A buffer: the first load that
     // lands there is issued in stage 0 of a tile, behind the prologue's
     // barrier, which every wave reaches after it read them
-    int &s_pos = reinterpret_cast<int *>(smem + 3 * SA)[-1];
-    int &s_ok = reinterpret_cast<int *>(smem + 3 * SA)[-2];
-    int &s_last = reinterpret_cast<int *>(smem + 3 * SA)[-3];
+    int &s_pos = reinterpret_cast<int *>(smem + NA * SA)[-1];
+    int &s_ok = reinterpret_cast<int *>(smem + NA * SA)[-2];
+    int &s_last = reinterpret_cast<int *>(smem + NA * SA)[-3];
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -331,28 +335,35 @@ void gemm_kernel(const GemmParams p) {
     uint64_t known = 0;   // partitions already acquired by this workgroup
     bool failed = false;
 
-    if (tid == 0) {
-        if (p.spread_wait > 0 && claim_cu_slot(p) > 0) {
-            // bounded: a scheduling preference, never a dependency
-            const uint32_t t_end = rtc32() + 1000u;   // 10 us of the 100 MHz counter
-            while ((int)ld_dev(&p.ctrl[v]) < p.spread_wait && (int32_t)(rtc32() - t_end) < 0)
-                __builtin_amdgcn_s_sleep(2);
-        }
-        const uint32_t c = __hip_atomic_fetch_add(&p.ctrl[v], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const int pos = ticket_position(p, v, c);
-        if (pos == 0 && p.start_word)
+    int pos, round = 0;
+    if (p.fixed) {
+        pos = static_position(p, (int)blockIdx.x, 0);
+        if (pos == 0 && p.start_word && tid == 0)
             __hip_atomic_store(p.start_word, p.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-        s_pos = pos;
+    } else {
+        if (tid == 0) {
+            if (p.spread_wait > 0 && claim_cu_slot(p) > 0) {
+                // bounded: a scheduling preference, never a dependency
+                const uint32_t t_end = rtc32() + 1000u;   // 10 us of the 100 MHz counter
+                while ((int)ld_dev(&p.ctrl[v]) < p.spread_wait && (int32_t)(rtc32() - t_end) < 0)
+                    __builtin_amdgcn_s_sleep(2);
+            }
+            const uint32_t c = __hip_atomic_fetch_add(&p.ctrl[v], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const int first = ticket_position(p, v, c);
+            if (first == 0 && p.start_word)
+                __hip_atomic_store(p.start_word, p.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+            s_pos = first;
+        }
+        __syncthreads();
+        pos = __builtin_amdgcn_readfirstlane(s_pos);
     }
-    __syncthreads();
-    int pos = __builtin_amdgcn_readfirstlane(s_pos);
 
-    while (pos < total) {
+    while (pos >= 0 && pos < total) {
         // work position -> (tile position, K slice); `split`: this tile's K
         // is split into `ns` slices, counted by split_cnt[uc], its partials
         // at workspace tiles [wsf, wsf + ns)
         const WorkItem wi = decode_item(p, pos);
-        const bool split = wi.split;
+        const bool split = kSplits && wi.split;
         const int tpos = wi.tpos, slice = wi.slice, ns = wi.ns, uc = wi.uc, wsf = wi.wsf, ksl = wi.ksl;
         const int kb = split ? slice * ksl : 0;
         const int ke = split ? min(p.K, kb + ksl) : p.K;
@@ -409,27 +420,27 @@ void gemm_kernel(const GemmParams p) {
                 return kc < ke ? (uint32_t)kc * 2u : kOOBCol;
             };
             const int KT = (ke - kb + kBK - 1) / kBK;
-            // LDS byte offsets: A of this stage, the next, the one after;
-            // W of this stage, the next
+            // LDS byte offsets of the buffers, rings of NA and DW
             const uint32_t lds0 = (uint32_t)(uintptr_t)LDS_AS(smem);
-            uint32_t aC = lds0, aN = aC + SA, aF = aN + SA, wC = aF + SA, wN = wC + SW;
-            // prologue: stages 0 and 1 in flight; stage 0 landed, its first
+            const uint32_t ldsW = lds0 + NA * SA, ldsE = ldsW + DW * SW;
+            // prologue: stages 0 to DW - 1 in flight; stage 0 landed, its first
             // fragments read (s_nop: resource words that came out of vector
             // registers need five wait states before a load reads them)
             i32x4 rA = rA0, rW = rW0;
             asm volatile("s_nop 4" : "+s"(rA), "+s"(rW));
-            load_blocks<LA>(rA, aC, offA, kcol(0), wave);
-            load_blocks<LW>(rW, wC, offW, kcol(0), wave);
-            load_blocks<LA>(rA, aN, offA, kcol(1), wave);
-            load_blocks<LW>(rW, wN, offW, kcol(1), wave);
-            wait_vm_lgkm0<LA + LW>();
+#pragma unroll
+            for (int i = 0; i < DW; ++i) {
+                load_blocks<LA>(rA, lds0 + i * SA, offA, kcol(i), wave);
+                load_blocks<LW>(rW, ldsW + i * SW, offW, kcol(i), wave);
+            }
+            wait_vm_lgkm0<(DW - 1) * (LA + LW)>();
             lds_barrier();
             bf16x8 a0[FM], b0[FN], a1[FM], b1[FN];
             const char *fa = smem + (wm0 + r) * 128;       // this lane's fragment rows, relative
             const char *fw = smem + (wn0 + r) * 128;       // to a buffer at smem + 0
             const int coff0 = (kq ^ swz) << 4, coff1 = ((4 + kq) ^ swz) << 4;
             {
-                const char *ca = fa + (aC - lds0) + coff0, *cw = fw + (wC - lds0) + coff0;
+                const char *ca = fa + coff0, *cw = fw + NA * SA + coff0;
 #pragma unroll
                 for (int mi = 0; mi < FM; ++mi) a0[mi] = *reinterpret_cast<const bf16x8 *>(ca + mi * 16 * 128);
 #pragma unroll
@@ -441,26 +452,38 @@ void gemm_kernel(const GemmParams p) {
             const uint32_t wb = (uint32_t)wave * 1024u;
             // Stage st on (aC, wC), its substep-0 fragments in (a0, b0), stage
             // st + 1 in flight in (aN, wN). Substep 0 (the first 32 of K) reads
-            // substep 1's fragments and issues the A loads of stage st + 2 into
+            // substep 1's fragments and issues the A loads of stage st + DW into
             // aF, which stage st - 1 freed. Substep 1 waits for all of stage
-            // st + 1 (the A loads just issued stay in flight), joins the
+            // st + 1 (the loads of later stages stay in flight), joins the
             // barrier, reads stage st + 1's first fragments and issues stage
-            // st + 2's W loads into wC, whose fragments every wave has read.
+            // st + DW's W loads into wC, whose fragments every wave has read.
+            uint32_t aC = lds0, aF = lds0 + DW * SA, wC = ldsW;
             for (int st = 0; st < KT; ++st) {
+                const uint32_t aN = aC + SA == ldsW ? lds0 : aC + SA, wN = wC + SW == ldsE ? ldsW : wC + SW;
                 const char *ca = fa + (aC - lds0), *cw = fw + (wC - lds0);
-                const uint32_t kc2 = kcol(st + 2);
+                const uint32_t kcf = kcol(st + DW);
+                // with one workgroup per CU the accumulators live in the
+                // accumulation registers: saying so here keeps every one of
+                // them in its own register around the loop (the compiler had
+                // MFMAs write a neighbouring one and moved up to 68 registers
+                // back per stage: 8192 x 6144 x 12288 855 against 811 us)
+                if constexpr (kAcc) {
+#pragma unroll
+                    for (int ni = 0; ni < FN; ++ni)
+#pragma unroll
+                        for (int mi = 0; mi < FM; ++mi) asm volatile("" : "+a"(acc[ni][mi]));
+                }
                 mfma_slots<0, NM, 0, RE, 0, LA, 0, NM, FM, FN>(acc, a0, b0, a1, b1, ca + coff1, cw + coff1, rA, aF + wb,
-                                                             offA, kc2);
+                                                             offA, kcf);
                 const char *na = fa + (aN - lds0) + coff0, *nw = fw + (wN - lds0) + coff0;
                 mfma_slots<0, B1, NM, NM + 1, 0, 0, 0, 1, FM, FN>(acc, a1, b1, a0, b0, na, nw, rW, 0u, offW, 0u);
-                wait_vm_lgkm0<LA>();
+                wait_vm_lgkm0<(DW - 1) * LA + (DW - 2) * LW>();
                 lds_barrier();
                 mfma_slots<B1, NM, B1, NM, 0, LW, B1, B1 + (NM - B1) * 3 / 4, FM, FN>(acc, a1, b1, a0, b0, na, nw, rW,
-                                                                                    wC + wb, offW, kc2);
-                const uint32_t t = aC;
-                aC = aN; aN = aF; aF = t;
-                const uint32_t u = wC;
-                wC = wN; wN = u;
+                                                                                    wC + wb, offW, kcf);
+                aF = aC;
+                aC = aN;
+                wC = wN;
             }
             // the loads issued past the end (zeros) land before the buffers
             // are reused
@@ -470,7 +493,7 @@ void gemm_kernel(const GemmParams p) {
 
         if (traced && tid == 0) t_loop = rtc32();
         // fetch the next ticket while the epilogue runs
-        if (tid == 0) {
+        if (!p.fixed && tid == 0) {
             const uint32_t c = __hip_atomic_fetch_add(&p.ctrl[v], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             s_pos = ticket_position(p, v, c);
         }
@@ -577,8 +600,9 @@ void gemm_kernel(const GemmParams p) {
                 // compile-time constant: the loads carry no branch, and the
                 // waits before the sums count them exactly.
                 auto finish_split = [&](auto b_const, auto s_const) {
-                    constexpr int B = decltype(b_const)::value, S = decltype(s_const)::value;
+                    constexpr int S = decltype(s_const)::value;
                     constexpr int NP = FM * FN / 2;   // pairs (mi, 2 nj), (mi, 2 nj + 1)
+                    constexpr int B = decltype(b_const)::value < NP ? decltype(b_const)::value : NP;
                     static_assert(NP % B == 0, "whole batches");
 #pragma unroll 1
                     for (int u0 = 0; u0 < NP; u0 += B) {
@@ -633,7 +657,7 @@ void gemm_kernel(const GemmParams p) {
             } else {
                 // Each wave turns 32 rows of its accumulators at a time to row
                 // order through a region of the freed stage buffers (FN * 2 KiB
-                // per wave: in A0 / A1 and in W0 / W1 by turns; 16-byte chunk c
+                // per wave: in the A and in the W buffers by turns; 16-byte chunk c
                 // of row r at chunk c ^ (r & 7)): written straight from the
                 // accumulation registers, read back 8 consecutive columns per
                 // lane, one 16-byte store of C each, whole rows of the wave's
@@ -644,8 +668,8 @@ void gemm_kernel(const GemmParams p) {
                 constexpr int CPR = 2 * FN;         // 8-column pieces per row
                 constexpr int NIT = 32 * CPR / 64;  // read-back rounds per 32 rows
                 constexpr int RB = FN * 64;         // bytes of one row in the region
-                static_assert(FM >= FN, "a region fits two A buffers");
-                char *const region[2] = {smem + wave * 32 * RB, smem + 3 * SA + wave * 32 * RB};
+                static_assert(4 * 32 * RB <= NA * SA - 16 && 4 * 32 * RB <= DW * SW, "a region fits its buffers");
+                char *const region[2] = {smem + wave * 32 * RB, smem + NA * SA + wave * 32 * RB};
                 const int el = et & 63;
                 auto to_lds = [&](int mi) {
                     char *w = region[mi & 1] + er * RB;
@@ -675,44 +699,41 @@ void gemm_kernel(const GemmParams p) {
                     }
                 };
                 if (has_p) {
-                    // The fp32 partial of 32 rows (two 16-byte loads per piece,
-                    // whole lines) is loaded while the rows before it are
-                    // stored. Loads and stores go through buffer resources
-                    // whose bound reads zeros / drops stores for rows or columns
-                    // outside C (or all of a failed tile), so the waits count
-                    // them exactly (no branch between them).
+                    // The fp32 partial (two 16-byte loads per piece, whole lines)
+                    // is loaded 8 pieces ahead. Loads and stores go through
+                    // buffer resources whose bound reads zeros / drops stores for
+                    // rows or columns outside C (or all of a failed tile), so the
+                    // waits count them exactly (no branch between them).
                     const int prow0 = map_row(p, m0);
                     const __amdgpu_buffer_rsrc_t rP =
                         tile_rsrc(pbase, pbytes, (uint64_t)(prow0 - plo) * (uint64_t)p.ldp * 4u);
                     const __amdgpu_buffer_rsrc_t rC =
                         tile_rsrc(p.C, p.c_bytes, (uint64_t)prow0 * (uint64_t)p.ldc * 2u);
-                    u32x4 pv[2][NIT][2];
-                    auto load_p = [&](int mi) {
-#pragma unroll
-                        for (int it = 0; it < NIT; ++it) {
-                            const int m = m0 + piece_row(mi, it), n = n0 + piece_col(it);
-                            const uint32_t off = (m < p.M && n < p.N)
-                                                     ? ((uint32_t)(map_row(p, m) - prow0) * (uint32_t)p.ldp + (uint32_t)n) * 4u
-                                                     : kOOBRow;
-                            pv[mi & 1][it][0] = __builtin_amdgcn_raw_buffer_load_b128(rP, off, 0, 0);
-                            pv[mi & 1][it][1] = __builtin_amdgcn_raw_buffer_load_b128(rP, off, 16, 0);
-                        }
+                    constexpr int NP = FM / 2 * NIT, AHEAD = NP < 8 ? NP : 8;
+                    u32x4 pv[AHEAD][2];
+                    auto load_p = [&](int i) {
+                        const int mi = i / NIT, it = i % NIT;
+                        const int m = m0 + piece_row(mi, it), n = n0 + piece_col(it);
+                        const uint32_t off = (m < p.M && n < p.N)
+                                                 ? ((uint32_t)(map_row(p, m) - prow0) * (uint32_t)p.ldp + (uint32_t)n) * 4u
+                                                 : kOOBRow;
+                        pv[i % AHEAD][0] = __builtin_amdgcn_raw_buffer_load_b128(rP, off, 0, 0);
+                        pv[i % AHEAD][1] = __builtin_amdgcn_raw_buffer_load_b128(rP, off, 16, 0);
                     };
-                    load_p(0);
+#pragma unroll
+                    for (int i = 0; i < AHEAD; ++i) load_p(i);
                     to_lds(0);
 #pragma unroll
                     for (int mi = 0; mi < FM / 2; ++mi) {
-                        if (mi + 1 < FM / 2) {
-                            load_p(mi + 1);
-                            to_lds(mi + 1);
-                        }
+                        if (mi + 1 < FM / 2) to_lds(mi + 1);
 #pragma unroll
                         for (int it = 0; it < NIT; ++it) {
                             float x[8];
                             from_lds(mi, it, x);
 #pragma unroll
                             for (int e = 0; e < 8; ++e)
-                                x[e] += __builtin_bit_cast(float, (uint32_t)pv[mi & 1][it][e >> 2][e & 3]);
+                                x[e] += __builtin_bit_cast(float, (uint32_t)pv[(mi * NIT + it) % AHEAD][e >> 2][e & 3]);
+                            if (mi * NIT + it + AHEAD < NP) load_p(mi * NIT + it + AHEAD);
                             const u32x4 o = {pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3]), pack_bf16x2(x[4], x[5]),
                                              pack_bf16x2(x[6], x[7])};
                             const int m = m0 + piece_row(mi, it), n = n0 + piece_col(it);
@@ -763,10 +784,15 @@ void gemm_kernel(const GemmParams p) {
             rec[0] = make_uint4((uint32_t)pos, ((uint32_t)rt << 16) | (uint32_t)tn, hw_id(), xcc_id());
             rec[1] = make_uint4(t_tick, t_gate, t_loop, rtc32());
         }
-        pos = __builtin_amdgcn_readfirstlane(s_pos);
+        if (p.fixed) {
+            pos = static_position(p, (int)blockIdx.x, ++round);
+        } else {
+            pos = __builtin_amdgcn_readfirstlane(s_pos);
+        }
     }
 
     // exit: the last workgroup out resets the shared counters
+    if (p.fixed && !(RS && p.done_host)) return;
     __syncthreads();
     if (tid == 0) {
         const uint32_t old = __hip_atomic_fetch_add(&p.ctrl[kCtrlExit], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -849,21 +875,27 @@ hipError_t launch_mfma_probe(uint64_t *out, int grid, int iters, hipStream_t str
     return hipGetLastError();
 }
 
+template <int BM, int BN, int DW>
+static void launch_tile(const GemmParams &p, bool rs, hipStream_t stream) {
+    if (rs && p.done_host)
+        hipLaunchKernelGGL((gemm_kernel<BM, BN, DW, true, true>), dim3(p.grid), dim3(kThreads), 0, stream, p);
+    else if (rs)
+        hipLaunchKernelGGL((gemm_kernel<BM, BN, DW, true>), dim3(p.grid), dim3(kThreads), 0, stream, p);
+    else
+        hipLaunchKernelGGL((gemm_kernel<BM, BN, DW, false>), dim3(p.grid), dim3(kThreads), 0, stream, p);
+}
+
 hipError_t launch_gemm(const GemmParams &p, int cfg, bool rs, hipStream_t stream) {
-    if (cfg == kTile256) {
-        if (rs && p.done_host)
-            hipLaunchKernelGGL((gemm_kernel<256, 256, true, true>), dim3(p.grid), dim3(kThreads), 0, stream, p);
-        else if (rs)
-            hipLaunchKernelGGL((gemm_kernel<256, 256, true>), dim3(p.grid), dim3(kThreads), 0, stream, p);
-        else
-            hipLaunchKernelGGL((gemm_kernel<256, 256, false>), dim3(p.grid), dim3(kThreads), 0, stream, p);
-    } else {
-        if (rs && p.done_host)
-            hipLaunchKernelGGL((gemm_kernel<128, 128, true, true>), dim3(p.grid), dim3(kThreads), 0, stream, p);
-        else if (rs)
-            hipLaunchKernelGGL((gemm_kernel<128, 128, true>), dim3(p.grid), dim3(kThreads), 0, stream, p);
-        else
-            hipLaunchKernelGGL((gemm_kernel<128, 128, false>), dim3(p.grid), dim3(kThreads), 0, stream, p);
+    switch (cfg) {
+    case kTile256: launch_tile<256, 256, 2>(p, rs, stream); break;
+    case kTile256x192: launch_tile<256, 192, 2>(p, rs, stream); break;
+    case kTile256x128: launch_tile<256, 128, 2>(p, rs, stream); break;
+    case kTile128: launch_tile<128, 128, 2>(p, rs, stream); break;
+    case kTile128Deep: launch_tile<128, 128, 4>(p, rs, stream); break;
+    case kTile128x64: launch_tile<128, 64, 2>(p, rs, stream); break;
+    case kTile128x64Deep: launch_tile<128, 64, 4>(p, rs, stream); break;
+    case kTile64: launch_tile<64, 64, 4>(p, rs, stream); break;
+    default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }

@@ -1,0 +1,111 @@
+// Tile shape and K split of a launch whose tiles do not wait for one another's
+// arrivals (plain GEMM, InterDecom sub-GEMMs, unfused baselines), from an
+// estimate of its time. Host only.
+#pragma once
+#include <algorithm>
+
+#include "kernel_params.h"
+
+namespace compass {
+
+struct Plan {
+    int cfg;      // TileCfg
+    int split;    // K slices per tile (1: whole)
+};
+
+// What may be split: the workspace's fp32 partial tiles, in bytes (0: nothing).
+struct PlanLimits {
+    int num_cu;
+    int slots_override;     // workgroups per launch (0: as many as the CUs hold)
+    uint64_t split_bytes;
+};
+
+constexpr int kMinSliceK = 512;     // K depth of a slice at least
+constexpr int kFewTiles = 4;        // 128 x 128 tiles of the smallest launches
+
+// Microseconds on MI355X (bf16, N(0, 1) data), fitted to launches of 8 to 192
+// stages of K = 64: a stage on one workgroup with most of the chip idle
+// (`alone`), a stage of every workgroup with all CUs holding as many as they
+// can (`full`: power bound for the large tiles, load bound for the small ones),
+// the tile's prologue and epilogue, and the factor on the stages when rows of
+// A and W do not start on 128-byte lines (K no multiple of 64: every row's
+// load touches two lines).
+struct TileCost { float alone, full, edge, ragged; };
+constexpr TileCost kTileCosts[kTileCfgs] = {
+    {0.984f, 1.365f, 6.9f, 1.05f},   // 256 x 256
+    {0.385f, 0.914f, 1.3f, 1.40f},   // 128 x 128, two per CU
+    {0.753f, 1.060f, 5.9f, 1.20f},   // 256 x 192
+    {0.537f, 0.787f, 3.7f, 1.40f},   // 256 x 128
+    {0.330f, 0.467f, 2.4f, 1.50f},   // 128 x 128 deep
+    {0.319f, 0.768f, 1.4f, 1.50f},   // 128 x 64, two per CU
+    {0.205f, 0.293f, 2.2f, 1.65f},   // 128 x 64 deep
+    {0.137f, 0.418f, 2.8f, 1.35f},   // 64 x 64, two per CU
+};
+
+inline int slices_of(int K, int split, int *kslice) {
+    *kslice = ((K + split - 1) / split + 63) / 64 * 64;
+    return (K + *kslice - 1) / *kslice;
+}
+
+// Estimated time of M x N x K in tiles of `cfg`, K in `split` slices.
+inline double plan_cost(int cfg, int split, int M, int N, int K, bool partial, const PlanLimits &lim) {
+    const TileShape &ts = kTileShapes[cfg];
+    const TileCost &tc = kTileCosts[cfg];
+    const double area = (double)ts.rows * ts.cols;
+    int kslice;
+    const int sp = slices_of(K, split, &kslice);
+    const long items = (long)((M + ts.rows - 1) / ts.rows) * ((N + ts.cols - 1) / ts.cols) * sp;
+    const long slots = lim.slots_override > 0 ? lim.slots_override : (long)lim.num_cu * ts.wg_per_cu;
+    const double stages = (std::min(kslice, K) + 63) / 64 * (K % 64 ? tc.ragged : 1.0);
+    // the partial's read, and, split, the completing slice's wait for the
+    // partial tiles' way through memory (uncached) and its sums over them
+    const double edge = tc.edge + (partial ? 6.0 * area * ts.wg_per_cu / 65536 : 0.0) +
+                        (sp > 1 ? (1.5 + sp * area * 4 / 65e3) * (items > lim.num_cu ? ts.wg_per_cu : 1) : 0.0);
+    const long rounds = items / slots, rest = items % slots;
+    double t = rounds * (stages * tc.full + edge);
+    if (rest) {
+        // a partly filled chip runs between the two stage times (the power
+        // the busy CUs draw sets the clock of all), and with some CUs holding
+        // two workgroups it ends with those
+        const double x = rest > lim.num_cu ? std::max(0.9, (double)rest / slots) : (double)rest / slots;
+        t += stages * (tc.alone + (tc.full - tc.alone) * x * x) + edge;
+    }
+    return t;
+}
+
+inline Plan plan_gemm(int M, int N, int K, bool partial, const PlanLimits &lim) {
+    auto allowed = [&](int cfg, int split) {
+        const TileShape &ts = kTileShapes[cfg];
+        const long tm = (M + ts.rows - 1) / ts.rows, tiles = tm * ((N + ts.cols - 1) / ts.cols);
+        if (tm > kMaxRowTiles) return false;
+        if (split == 1) return true;
+        const long slots = lim.slots_override > 0 ? lim.slots_override : (long)lim.num_cu * ts.wg_per_cu;
+        // one round of slices (the workspace holds a launch's partial tiles)
+        return ts.rows > 64 && K / split >= kMinSliceK && tiles <= kMaxSplitTiles && tiles * split <= slots &&
+               (uint64_t)tiles * split * ts.rows * ts.cols * 4 <= lim.split_bytes;
+    };
+    // the smallest launches: as many K slices as their depth holds. (256 x 256,
+    // K = 2560 to 4096; the estimate's differences there are below its error)
+    const long t128 = (long)((M + 127) / 128) * ((N + 127) / 128);
+    if (t128 <= kFewTiles && M > 128 && N > 128) {
+        int sp = std::min(kMaxSplit, std::max(1, K / kMinSliceK));
+        while (sp > 1 && !allowed(kTile128, sp)) --sp;
+        int kslice;
+        return {kTile128, slices_of(K, sp, &kslice)};
+    }
+    Plan best{kTile128, 1};
+    double tb = 1e30;
+    for (int cfg = 0; cfg < kTileCfgs; ++cfg)
+        for (int sp = 1; sp <= kMaxSplit; ++sp) {
+            if (!allowed(cfg, sp)) continue;
+            const double t = plan_cost(cfg, sp, M, N, K, partial, lim);
+            if (t < tb) {
+                tb = t;
+                int kslice;
+                best = {cfg, slices_of(K, sp, &kslice)};
+            }
+        }
+    return best;
+}
+
+}  // namespace compass

@@ -47,6 +47,7 @@
 #include "compass.h"
 #include "internal.h"
 #include "kernel_params.h"
+#include "plan.h"
 
 namespace compass {
 
@@ -86,7 +87,6 @@ constexpr size_t kPoolSlice = 3u << 20;
 constexpr int kSchedFineQueues = 1, kSchedSpread = 2, kSchedSplitK = 4;
 // split-K workspace: one fp32 partial tile per workgroup slot (the largest
 // of 256 x 256 on one workgroup per CU and 128 x 128 on two)
-constexpr int kMinSliceK = 512;      // K depth of a slice at least
 constexpr int kSplitWsTiles = 3;     // workspace: this many 256 x 256 fp32 partial tiles per CU
 constexpr int kTailMinK = 8192;      // fused AllGather: split the tail's K from this depth on
 constexpr int kTailSliceK = 2048;    // ... into slices at least this deep, at most 4
@@ -1178,29 +1178,26 @@ static void init_params(GemmParams &g, uint32_t epoch) {
     g.epoch = epoch;
 }
 
-static int pick_tile(int M, int N, bool gated, int prow = 0, double lam_est = 0.0, bool rs = false) {
+// Tile of a fused operator (prow: rows of its smallest partition).
+static int pick_tile(int M, int N, int prow, double lam_est, bool rs) {
     if (g_ctx.tile_override == 1) return kTile256;
     if (g_ctx.tile_override == 2) return kTile128;
-    // A plain GEMM takes the larger (faster) tile when it still fills every
-    // CU. The fused AllGather needs several tiles per arriving partition; it
-    // takes it when a partition spans whole 256-row tiles and the GEMM is at
-    // least two waves of 256 x 256 tiles (the tiles of the last arrivals then
-    // split K, see set_tail_split): on the GPT-3 AllGather (3 waves, 4 : 1
-    // double ring, lambda ~ 1) 1156 us against 1361 us with 128 x 128 tiles,
-    // whose main loop runs ~15 % slower per flop.
+    // The fused AllGather needs several tiles per arriving partition; it
+    // takes the larger (faster) tile when a partition spans whole 256-row
+    // tiles and the GEMM is at least two waves of 256 x 256 tiles (the tiles
+    // of the last arrivals then split K, see set_tail_split): on the GPT-3
+    // AllGather (3 waves, 4 : 1 double ring, lambda ~ 1) 1156 us against
+    // 1361 us with 128 x 128 tiles, whose main loop runs slower per flop.
     // The fused ReduceScatter takes 256 x 256 only when computation dominates
     // (estimated lambda >= 1) over at least two waves: with one workgroup per
     // CU its chunks finish in bursts of a whole wave and the sends of the last
     // burst trail the kernel, which the faster GEMM repays only when the
     // transfer is the smaller part.
     const long t256 = (long)((M + 255) / 256) * ((N + 255) / 256);
-    if (gated) {
-        const bool whole = prow >= 256 && prow % 256 == 0;
-        const long cu = g_ctx.num_cu;
-        if (rs) return whole && t256 >= 2 * cu && lam_est >= 1.0 ? kTile256 : kTile128;
-        return whole && t256 >= 2 * cu ? kTile256 : kTile128;
-    }
-    return t256 >= g_ctx.num_cu ? kTile256 : kTile128;
+    const bool whole = prow >= 256 && prow % 256 == 0;
+    const long cu = g_ctx.num_cu;
+    if (rs) return whole && t256 >= 2 * cu && lam_est >= 1.0 ? kTile256 : kTile128;
+    return whole && t256 >= 2 * cu ? kTile256 : kTile128;
 }
 
 // Rough comp/comm ratio of a fused operator, used only to pick its tile: the
@@ -1251,7 +1248,7 @@ static int set_shape(GemmParams &g, int cfg, int M, int N, int K, const void *A,
     g.grid = std::max(1, std::min(total, cap));
     g.nq = g.grid >= kMaxQueues ? kMaxQueues : 1;
     g.q_size = std::max(1, g.grid / g.nq);
-    g.group_m = cfg == kTile256 ? 4 : 8;
+    g.group_m = tile_rows(cfg) == 256 ? 4 : 8;
     for (int t = 0; t < g.tiles_m; ++t) {
         g.rt_order[t] = (uint16_t)t;
         g.rt_lo[t] = 0;
@@ -1260,31 +1257,35 @@ static int set_shape(GemmParams &g, int cfg, int M, int N, int K, const void *A,
     return COMPASS_OK;
 }
 
-// Split K for a launch with too few tiles to occupy every workgroup slot:
-// s slices per tile (at most kMaxSplit, each at least kMinSliceK deep, K
-// slices multiples of 64), s * tiles <= slots, so that every slot gets a
-// slice and the partials fit the workspace.
-static void set_split(GemmParams &g, int cfg) {
+// Tile shape and K split of a launch that plan_gemm plans, with the options
+// that restrict it: COMPASS_OPT_TILE (that tile, as many slices as fill its
+// slots, each at least kMinSliceK deep), COMPASS_OPT_GRID and the split bit of
+// COMPASS_OPT_SCHED.
+static Plan plan_launch(int M, int N, int K, bool partial) {
     Ctx &c = g_ctx;
-    const int tiles = g.tiles_m * g.tiles_n;
-    const int slots = g_ctx.grid_override > 0 ? g_ctx.grid_override : c.num_cu * tile_wg_per_cu(cfg);
-    if (!(c.sched & kSchedSplitK) || !c.split_ws || tiles > kMaxSplitTiles || 2 * tiles > slots) return;
-    // at most 8 slices: the slice that completes a tile reads every partial,
-    // and past 8 that costs more than the finer split gains (InterDecom at
-    // d = 16 on the QKV shape: 850 us with up to 16 slices, 756 us with 8)
-    int sp = std::min(std::min(slots / tiles, kMaxSplit), std::max(1, g.K / kMinSliceK));
-    if (sp < 2) return;
+    const bool may_split = (c.sched & kSchedSplitK) && c.split_ws;
+    const PlanLimits lim{c.num_cu, c.grid_override, may_split ? (uint64_t)c.split_ws_bytes : 0};
+    if (c.tile_override == 0) return plan_gemm(M, N, K, partial, lim);
+    const int cfg = c.tile_override == 1 ? kTile256 : kTile128;
+    const long tiles = (long)((M + tile_rows(cfg) - 1) / tile_rows(cfg)) * ((N + tile_cols(cfg) - 1) / tile_cols(cfg));
+    const long slots = c.grid_override > 0 ? c.grid_override : (long)c.num_cu * tile_wg_per_cu(cfg);
+    if (!may_split || tiles > kMaxSplitTiles || 2 * tiles > slots) return {cfg, 1};
+    int sp = (int)std::min<long>(std::min<long>(slots / tiles, kMaxSplit), std::max(1, K / kMinSliceK));
     const size_t tile_bytes = (size_t)tile_rows(cfg) * tile_cols(cfg) * sizeof(float);
     while (sp > 1 && (size_t)tiles * sp * tile_bytes > c.split_ws_bytes) --sp;
-    if (sp < 2) return;
-    const int kslice = ((g.K + sp - 1) / sp + 63) / 64 * 64;
-    sp = (g.K + kslice - 1) / kslice;
-    if (sp < 2) return;
-    g.ksplit = sp;
-    g.kslice = kslice;
-    g.grid = std::min(tiles * sp, slots);
-    g.nq = g.grid >= kMaxQueues ? kMaxQueues : 1;
-    g.q_size = std::max(1, g.grid / g.nq);
+    int kslice;
+    return {cfg, slices_of(K, sp, &kslice)};
+}
+
+// The plan's split (set_shape has set the tiles), and positions dealt without
+// tickets.
+static void apply_plan(GemmParams &g, const Plan &pl) {
+    const int slots = g_ctx.grid_override > 0 ? g_ctx.grid_override : g_ctx.num_cu * tile_wg_per_cu(pl.cfg);
+    g.fixed = 1;
+    if (pl.split > 1) {
+        g.ksplit = slices_of(g.K, pl.split, &g.kslice);
+        g.grid = std::min(g.tiles_m * g.tiles_n * g.ksplit, slots);
+    }
 }
 
 // Tail split of a fused AllGather with 256 x 256 tiles: a tile runs K / 64
@@ -1927,7 +1928,7 @@ int op_ag_gemm(const compass_problem *p, const compass_links *l, void *stream) {
     // (rate-proportional parts: a 256-row tile may span both parts of a
     // chunk and waits for the later one, which an AllGather tolerates)
     const double lam = lambda_estimate(p, geo, l);
-    const int cfg = pick_tile(p->M, p->N, true, geo.fb != 0.5 && geo.sub == 1 ? geo.rows : min_part_rows(geo), lam);
+    const int cfg = pick_tile(p->M, p->N, geo.fb != 0.5 && geo.sub == 1 ? geo.rows : min_part_rows(geo), lam, false);
     if ((rc = set_shape(g, cfg, p->M, p->N, p->K, p->gathered, p->M, p->W, p->C, nullptr)) != COMPASS_OK) return rc;
     // 256-row tiles: one row-tile group per partition, so that the dealing
     // and the tail split follow partitions
@@ -1942,6 +1943,7 @@ int op_ag_gemm(const compass_problem *p, const compass_links *l, void *stream) {
     g.nparts = geo.P;
     g.resident_mask = resident_mask(p, geo);
     g.start_word = &g_ctx.hw[kHwStart];
+    g.fixed = g.spread_wait == 0 && work_items(g) <= g.grid;
     submit(0, std::move(ag[0]));
     submit(1, std::move(ag[1]));
     return launch(g, cfg, false, s);
@@ -1959,7 +1961,7 @@ int op_gemm_rs(const compass_problem *p, const compass_links *l, void *stream) {
     if ((rc = rs_jobs(p, geo, l, epoch, 1, res, true, true, jobs)) != COMPASS_OK) return rc;
     GemmParams g;
     init_params(g, epoch);
-    const int cfg = pick_tile(p->M, p->N, true, min_part_rows(geo), lambda_estimate(p, geo, l), true);
+    const int cfg = pick_tile(p->M, p->N, min_part_rows(geo), lambda_estimate(p, geo, l), true);
     if ((rc = set_shape(g, cfg, p->M, p->N, p->K, p->A, p->M, p->W, p->C, p->partial_stage)) != COMPASS_OK) return rc;
     bool aliased = false;
     if ((rc = alias_resident_partials(g, p, geo, res, cfg, &aliased)) != COMPASS_OK) return rc;
@@ -1992,6 +1994,7 @@ int op_gemm_rs(const compass_problem *p, const compass_links *l, void *stream) {
         for (int r = 2; r < 4; ++r)
             if (jobs[r].final_flag >= 0) finals.push_back(jobs[r].final_flag);
     }
+    g.fixed = work_items(g) <= g.grid;
     pool_jobs(jobs, 4);
     for (int r = 0; r < 4; ++r) submit(r, std::move(jobs[r]));
     if ((rc = launch(g, cfg, true, s)) != COMPASS_OK) return rc;
@@ -2037,7 +2040,8 @@ int op_decomp(const compass_problem *p, int d, const compass_links *l, void *str
                 if (rs[r].final_flag >= 0) finals.push_back(rs[r].final_flag);
     }
     std::vector<GemmParams> launches(d);
-    const int cfg = pick_tile(p->M / d, p->N, false);
+    const Plan pl = plan_launch(p->M / d, p->N, p->K, p->pattern == COMPASS_GEMM_RS);
+    const int cfg = pl.cfg;
     for (int j = 0; j < d; ++j) {
         GemmParams &g = launches[j];
         init_params(g, epoch);
@@ -2062,7 +2066,7 @@ int op_decomp(const compass_problem *p, int d, const compass_links *l, void *str
             for (int q = 0; q < geo.P; ++q)
                 if (g.send_mask & (1ull << q)) g.done_expect[q] = (uint32_t)(g.tiles_m * g.tiles_n);
         }
-        set_split(g, cfg);
+        apply_plan(g, pl);
     }
     if (p->pattern == COMPASS_AG_GEMM) {
         pool_jobs(agj, 2);
@@ -2089,11 +2093,11 @@ int op_gemm(int M, int N, int K, const void *A, const void *W, void *C, const fl
     if (rc != COMPASS_OK) return rc;
     GemmParams g;
     init_params(g, g_ctx.epoch);
-    const int cfg = pick_tile(M, N, false);
-    if ((rc = set_shape(g, cfg, M, N, K, A, M, W, C, P)) != COMPASS_OK) return rc;
+    const Plan pl = plan_launch(M, N, K, P != nullptr);
+    if ((rc = set_shape(g, pl.cfg, M, N, K, A, M, W, C, P)) != COMPASS_OK) return rc;
     g.gate = kGateNone;
-    set_split(g, cfg);
-    return launch(g, cfg, P != nullptr, (hipStream_t)stream);
+    apply_plan(g, pl);
+    return launch(g, pl.cfg, P != nullptr, (hipStream_t)stream);
 }
 
 int op_transfer(const compass_problem *p, const compass_links *l, void *stream) {
@@ -2140,13 +2144,14 @@ int op_sequential(const compass_problem *p, const compass_links *l, void *stream
     if ((rc = rs_jobs(p, geo, l, epoch, 1, res, false, true, jobs)) != COMPASS_OK) return rc;
     GemmParams g;
     init_params(g, epoch);
-    const int cfg = pick_tile(p->M, p->N, false);
+    const Plan pl = plan_launch(p->M, p->N, p->K, true);
+    const int cfg = pl.cfg;
     if ((rc = set_shape(g, cfg, p->M, p->N, p->K, p->A, p->M, p->W, p->C, p->partial_stage)) != COMPASS_OK) return rc;
     bool aliased = false;
     if ((rc = alias_resident_partials(g, p, geo, res, cfg, &aliased)) != COMPASS_OK) return rc;
     if (!aliased && (rc = stage_resident_partials(p, geo, res, 1, s)) != COMPASS_OK) return rc;
     g.gate = kGateNone;
-    set_split(g, cfg);
+    apply_plan(g, pl);
     if ((rc = launch(g, cfg, true, s)) != COMPASS_OK) return rc;
     std::vector<int> wait;
     for (int r = 0; r < 2; ++r)

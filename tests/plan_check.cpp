@@ -1,0 +1,87 @@
+// Host check of the launch plan (plan.h) and of the fixed work positions
+// (kernel_params.h: static_position): over a grid of GEMM sizes, odd ones among
+// them, the plan's row tiles fit the row-tile table, a split fits one round of
+// workgroups, the split counters and the workspace, no slice is empty, and the
+// rounds of all workgroups take every work position once. The sizes given as
+// arguments ("M,N,K,partial,cfg,split") must get that tile and split.
+// Prints "ok <sizes>" or the first failure.
+#include <cstdio>
+#include <cstring>
+#include <vector>
+
+#define __host__
+#define __device__
+#include "plan.h"
+
+using namespace compass;
+
+static GemmParams params(int M, int N, int K, const Plan &pl, int num_cu) {
+    GemmParams g;
+    std::memset(&g, 0, sizeof g);
+    const TileShape &ts = kTileShapes[pl.cfg];
+    g.tiles_m = (M + ts.rows - 1) / ts.rows;
+    g.tiles_n = (N + ts.cols - 1) / ts.cols;
+    g.K = K;
+    g.kslice = K;
+    g.ksplit = 1;
+    g.group_m = ts.rows == 256 ? 4 : 8;
+    const int slots = num_cu * ts.wg_per_cu;
+    if (pl.split > 1) g.ksplit = slices_of(K, pl.split, &g.kslice);
+    g.grid = std::min(g.tiles_m * g.tiles_n * g.ksplit, slots);
+    return g;
+}
+
+static bool check(int M, int N, int K, bool partial, const PlanLimits &lim, char *why) {
+    const Plan pl = plan_gemm(M, N, K, partial, lim);
+    if (pl.cfg < 0 || pl.cfg >= kTileCfgs || pl.split < 1 || pl.split > kMaxSplit) { std::sprintf(why, "plan %d/%d", pl.cfg, pl.split); return false; }
+    const GemmParams g = params(M, N, K, pl, lim.num_cu);
+    const TileShape &ts = kTileShapes[pl.cfg];
+    if (g.tiles_m > kMaxRowTiles) { std::sprintf(why, "%d row tiles", g.tiles_m); return false; }
+    const int tiles = g.tiles_m * g.tiles_n;
+    if (pl.split > 1) {
+        if (g.ksplit != pl.split) { std::sprintf(why, "%d slices for a plan of %d", g.ksplit, pl.split); return false; }
+        if (ts.rows <= 64) { std::sprintf(why, "the smallest tile split"); return false; }
+        if (tiles > kMaxSplitTiles || (long)tiles * g.ksplit > (long)lim.num_cu * ts.wg_per_cu ||
+            (uint64_t)tiles * g.ksplit * ts.rows * ts.cols * 4 > lim.split_bytes) { std::sprintf(why, "split out of bounds"); return false; }
+        if ((g.ksplit - 1) * g.kslice >= K || g.kslice % 64) { std::sprintf(why, "slice %d of K %d", g.kslice, K); return false; }
+    }
+    const int all = work_items(g);
+    std::vector<char> seen(all, 0);
+    for (int b = 0; b < g.grid; ++b)
+        for (int j = 0;; ++j) {
+            const int pos = static_position(g, b, j);
+            if (pos < 0) break;
+            if (pos >= all || seen[pos]++) { std::sprintf(why, "position %d of %d by workgroup %d round %d", pos, all, b, j); return false; }
+        }
+    for (int p = 0; p < all; ++p)
+        if (!seen[p]) { std::sprintf(why, "position %d of %d left out", p, all); return false; }
+    return true;
+}
+
+int main(int argc, char **argv) {
+    const PlanLimits split{256, 0, 3ull * 256 * 256 * 256 * 4}, whole{256, 0, 0}, small{4, 0, 3ull * 4 * 256 * 256 * 4};
+    char why[256];
+    int count = 0;
+    const int Ms[] = {1, 15, 64, 65, 127, 129, 257, 640, 1000, 2049, 4096, 8191, 32768, 32769, 65536};
+    const int Ns[] = {8, 72, 256, 776, 2048, 3080, 12288};
+    const int Ks[] = {8, 64, 200, 512, 1032, 4096, 8192, 12296};
+    for (int M : Ms)
+        for (int N : Ns)
+            for (int K : Ks)
+                for (int p = 0; p < 2; ++p)
+                    for (const PlanLimits &lim : {split, whole, small}) {
+                        ++count;
+                        if (!check(M, N, K, p, lim, why)) {
+                            std::printf("FAIL %d x %d x %d partial %d cus %d: %s\n", M, N, K, p, lim.num_cu, why);
+                            return 1;
+                        }
+                    }
+    for (int i = 1; i < argc; ++i) {
+        int M, N, K, p, cfg, sp;
+        if (std::sscanf(argv[i], "%d,%d,%d,%d,%d,%d", &M, &N, &K, &p, &cfg, &sp) != 6) { std::printf("FAIL argument %s\n", argv[i]); return 1; }
+        const Plan pl = plan_gemm(M, N, K, p, split);
+        if (pl.cfg != cfg || pl.split != sp) { std::printf("FAIL %s: plan %d/%d\n", argv[i], pl.cfg, pl.split); return 1; }
+    }
+    std::printf("ok %d\n", count);
+    return 0;
+}

@@ -3,7 +3,8 @@ work_items, decode_item, tile_of), compiled for the host with g++ and checked
 over a grid of launch shapes and split settings (tests/decode_check.cpp):
 every work position is one (tile, K slice), every tile's K is covered once,
 split counters and workspace tiles are distinct and within bounds, and the
-tile walk is a bijection."""
+tile walk is a bijection. The launch plan (plan.h) is checked the same way
+(tests/plan_check.cpp)."""
 import os
 import shutil
 import subprocess
@@ -23,3 +24,15 @@ def test_work_item_decode_is_a_bijection(tmp_path):
     assert out.returncode == 0, out.stdout + out.stderr
     assert out.stdout.startswith("ok "), out.stdout
     assert int(out.stdout.split()[1]) > 10000
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs a host C++ compiler")
+def test_launch_plans_stay_in_bounds_and_take_every_position(tmp_path):
+    from tests.gpu_helpers import PLAN_SIZES
+    exe = tmp_path / "plan_check"
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", f"-I{CSRC}", "-o", str(exe),
+                    os.path.join(HERE, "plan_check.cpp")], check=True)
+    sizes = [",".join(str(int(v)) for v in x) for x in PLAN_SIZES]
+    out = subprocess.run([str(exe)] + sizes, capture_output=True, text=True, timeout=120)
+    assert out.returncode == 0, out.stdout + out.stderr
+    assert out.stdout.startswith("ok "), out.stdout

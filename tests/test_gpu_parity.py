@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 import oracle as O  # noqa: E402
 from paper_2609_10549_amd import compass as C  # noqa: E402
 from synth import make_ag_inputs, make_int_ag_inputs, make_int_rs_inputs, make_rs_inputs  # noqa: E402
-from tests.gpu_helpers import TOL, AGCase, RSCase, host_bits, host_f64, rel_err, dev_bits  # noqa: E402
+from tests.gpu_helpers import PLAN_SIZES, TOL, AGCase, RSCase, host_bits, host_f64, rel_err, dev_bits  # noqa: E402
 
 FAST = C.links(200e9, 200e9)   # emulated link rates for functional tests
 
@@ -545,12 +545,27 @@ def test_stage_counts_integer_exact(tile_cfg, K, partial):
     inp = make_int_rs_inputs(M, N, K, 1, seed=K)
     A, W = dev_bits(inp["A"]), dev_bits(inp["W"])
     Cm = torch.zeros((M, N), dtype=torch.int16, device="cuda")
-    P = dev_f32(inp["P_in"][0]) if partial else None
+    P = torch.from_numpy(inp["P_in"][0]).cuda() if partial else None
     C.compass_gemm(A, W, Cm, P)
     torch.cuda.synchronize()
     pin = inp["P_in"][0].astype(np.float64) if partial else np.zeros((M, N))
     ref = O.gemm_rs(O.bf16_to_f64(inp["A"]), O.bf16_to_f64(inp["W"]), [pin], 1)
     assert np.array_equal(host_bits(Cm), O.f64_to_bf16_rne(ref))
+
+
+@pytest.mark.parametrize("M,N,K,partial,cfg,split", PLAN_SIZES)
+def test_every_tile_and_split_integer_exact(M, N, K, partial, cfg, split):
+    _say("plan", M, N, K, partial, cfg, split)
+    inp = make_int_rs_inputs(M, N, K, 1, seed=M + N + K)
+    A, W = dev_bits(inp["A"]), dev_bits(inp["W"])
+    P = torch.from_numpy(inp["P_in"][0]).cuda() if partial else None
+    pin = inp["P_in"][0].astype(np.float64) if partial else np.zeros((M, N))
+    ref = O.f64_to_bf16_rne(O.gemm_rs(O.bf16_to_f64(inp["A"]), O.bf16_to_f64(inp["W"]), [pin], 1))
+    for fn in (C.compass_gemm, C.compass_gemm_noalloc):   # the latter: the best plan that splits nothing
+        Cm = torch.full((M, N), 0x7FC0, dtype=torch.int16, device="cuda")
+        fn(A, W, Cm, P)
+        torch.cuda.synchronize()
+        assert np.array_equal(host_bits(Cm), ref), fn.__name__
 
 
 # ------------------------------------------------------------ per-launch kernel timing

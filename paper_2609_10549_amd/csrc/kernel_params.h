@@ -137,6 +137,15 @@ struct GemmParams {
     uint32_t done_expect[kMaxParts];   // tiles per partition to count (0: none)
 };
 
+// Few-row GEMM (skinny_kernel): C = A W^T (+ P), densely packed.
+constexpr int kSkinnyRows = 64;
+struct SkinnyParams {
+    const uint16_t *A, *W;
+    uint16_t *C;
+    const float *P;   // or null
+    int M, N, K;
+};
+
 struct JoinParams {
     uint32_t *flags;
     uint32_t *start_word;   // written with epoch first (or null)

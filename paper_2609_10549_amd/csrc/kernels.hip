@@ -807,6 +807,112 @@ void gemm_kernel(const GemmParams p) {
     }
 }
 
+// Few rows (at most 16 MT): C of 16 columns per workgroup, K dealt to its NW
+// waves one stage (64) at a time. Each wave streams its own stages of A and W
+// through a ring of NST buffers of its own in LDS, so no barrier joins the
+// waves before their partial sums are added (in wave order) at the end.
+//
+// What bounds it: the bytes a CU can pull through its L1 (64 per clock), A's
+// rows once per 16 columns beside W's: hence the narrow tile, which spreads W
+// over N / 16 CUs, and NST - 1 stages of loads in flight per wave. 48 x 3072 x
+// 8192: 25.2 us in 64 x 64 tiles (48 CUs busy, a barrier per stage), 15.8
+// here (50 MB of W at 3.2 TB/s with the launch, 4.6 TB/s without).
+template <int MT, int NW, int NST>
+__global__ __launch_bounds__(NW * 64) void skinny_kernel(const SkinnyParams p) {
+    constexpr int SB = (MT + 1) * 2048;   // A rows, then W rows, 128 bytes each
+    constexpr int L = 2 * MT + 2;         // loads per stage
+    static_assert(NW * NST * SB <= (160 << 10) && NW * MT * 1024 <= NW * NST * SB, "LDS");
+    __shared__ __attribute__((aligned(1024))) char smem[NW * NST * SB];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n0 = (int)blockIdx.x * 16;
+    i32x4 rA = tile_rsrc4(p.A, (uint64_t)p.M * (uint64_t)p.K * 2u, 0);
+    i32x4 rW = tile_rsrc4(p.W, (uint64_t)p.N * (uint64_t)p.K * 2u, (uint64_t)n0 * (uint64_t)p.K * 2u);
+    asm volatile("s_nop 4" : "+s"(rA), "+s"(rW));   // as in gemm_kernel
+    // load j covers rows 8 j + (lane >> 3); the lane takes the chunk that the
+    // permutation (row >> 1) & 7 puts at its physical chunk lane & 7
+    uint32_t offA[2 * MT], offW[2];
+#pragma unroll
+    for (int j = 0; j < 2 * MT; ++j) {
+        const int row = 8 * j + (lane >> 3);
+        offA[j] = row < p.M ? (uint32_t)row * (uint32_t)p.K * 2u : kOOBRow;
+    }
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const int row = 8 * j + (lane >> 3);
+        offW[j] = n0 + row < p.N ? (uint32_t)row * (uint32_t)p.K * 2u : kOOBRow;
+    }
+    const int c0 = (lane & 7) ^ (lane >> 4), c1 = (lane & 7) ^ (4 + (lane >> 4));
+    const uint32_t ring = (uint32_t)(uintptr_t)LDS_AS(smem) + (uint32_t)(wave * NST * SB);
+    const int KT = (p.K + kBK - 1) / kBK;
+    auto load_stage = [&](int st, uint32_t buf) {
+        const int k0 = st * kBK + c0 * 8, k1 = st * kBK + c1 * 8;
+        const uint32_t q0 = k0 < p.K ? (uint32_t)k0 * 2u : kOOBCol, q1 = k1 < p.K ? (uint32_t)k1 * 2u : kOOBCol;
+#pragma unroll
+        for (int j = 0; j < 2; ++j) dma16(rW, offW[j] + (j & 1 ? q1 : q0), buf + (2 * MT + j) * 1024);
+#pragma unroll
+        for (int j = 0; j < 2 * MT; ++j) dma16(rA, offA[j] + (j & 1 ? q1 : q0), buf + j * 1024);
+    };
+    f32x4 acc[MT];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) acc[mt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    const int r = lane & 15, kq = lane >> 4, swz = (r >> 1) & 7;
+    const char *frag = smem + wave * NST * SB + r * 128;
+#pragma unroll
+    for (int i = 0; i < NST; ++i) load_stage(wave + i * NW, ring + i * SB);   // (past the end: zeros)
+    uint32_t slot = 0;
+    for (int st = wave; st < KT; st += NW) {
+        wait_vm_lgkm0<(NST - 1) * L>();
+        bf16x8 a[2][MT], b[2];
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk) {
+            const char *f = frag + slot + (((4 * kk + kq) ^ swz) << 4);
+            b[kk] = *reinterpret_cast<const bf16x8 *>(f + MT * 2048);
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) a[kk][mt] = *reinterpret_cast<const bf16x8 *>(f + mt * 2048);
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the stage is in registers before its buffer is refilled
+        load_stage(st + NST * NW, ring + slot);
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+                acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[kk], a[kk][mt], acc[mt], 0, 0, 0);
+        slot = slot + SB == NST * SB ? 0u : slot + SB;
+    }
+    wait_vm_lgkm0<0>();   // the loads issued past the end have landed
+    __syncthreads();
+    // partial sums [wave][row][16 columns]
+    f32x4 *sum = reinterpret_cast<f32x4 *>(smem);
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) sum[(wave * MT * 16 + mt * 16 + r) * 4 + kq] = acc[mt];
+    __syncthreads();
+    if (tid < MT * 64) {
+        const int row = tid >> 2, n = n0 + (tid & 3) * 4;
+        if (row < p.M && n < p.N) {
+            f32x4 x = sum[tid];
+#pragma unroll
+            for (int w = 1; w < NW; ++w) x += sum[w * MT * 64 + tid];
+            const size_t o = (size_t)row * p.N + n;
+            if (p.P) x += *reinterpret_cast<const f32x4 *>(p.P + o);
+            *reinterpret_cast<u32x2 *>(p.C + o) = u32x2{pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3])};
+        }
+    }
+}
+
+hipError_t launch_skinny(const SkinnyParams &p, hipStream_t stream) {
+    const dim3 grid((p.N + 15) / 16);
+    if (p.M <= 16)
+        hipLaunchKernelGGL((skinny_kernel<1, 8, 4>), grid, dim3(512), 0, stream, p);
+    else if (p.M <= 32)
+        hipLaunchKernelGGL((skinny_kernel<2, 8, 3>), grid, dim3(512), 0, stream, p);
+    else if (p.M <= 48)
+        hipLaunchKernelGGL((skinny_kernel<3, 4, 5>), grid, dim3(256), 0, stream, p);
+    else
+        hipLaunchKernelGGL((skinny_kernel<4, 4, 4>), grid, dim3(256), 0, stream, p);
+    return hipGetLastError();
+}
+
 __global__ __launch_bounds__(64) void join_kernel(const JoinParams j) {
     if (threadIdx.x != 0) return;
     if (j.start_word) __hip_atomic_store(j.start_word, j.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);

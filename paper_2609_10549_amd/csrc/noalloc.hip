@@ -21,6 +21,7 @@
 namespace compass {
 
 hipError_t launch_gemm(const GemmParams &p, int cfg, bool rs, hipStream_t stream);
+hipError_t launch_skinny(const SkinnyParams &p, hipStream_t stream);
 
 namespace {
 
@@ -70,10 +71,17 @@ int op_gemm_noalloc(int M, int N, int K, const void *A, const void *W, void *C, 
     int rc = current_num_cu(&num_cu);
     if (rc != COMPASS_OK) return rc;
 
+    hipStream_t s = (hipStream_t)stream;
+    // compass_gemm's choice among the plans that split no K
+    const PlanLimits lim{num_cu, 0, 0};
+    const Plan pl = plan_gemm(M, N, K, P != nullptr, lim);
+    if (skinny_faster(M, N, K, P != nullptr, pl, lim)) {
+        const hipError_t e = launch_skinny({(const uint16_t *)A, (const uint16_t *)W, (uint16_t *)C, P, M, N, K}, s);
+        return e == hipSuccess ? COMPASS_OK : hip_error(e, "GEMM launch");
+    }
+    const int cfg = pl.cfg;
     GemmParams g;
     std::memset(&g, 0, sizeof g);
-    // compass_gemm's choice among the plans that split no K
-    const int cfg = plan_gemm(M, N, K, P != nullptr, PlanLimits{num_cu, 0, 0}).cfg;
     const int bm = tile_rows(cfg), bn = tile_cols(cfg);
     g.A = (const uint16_t *)A;
     g.W = (const uint16_t *)W;
@@ -103,7 +111,6 @@ int op_gemm_noalloc(int M, int N, int K, const void *A, const void *W, void *C, 
     g.gate = kGateNone;
     for (int t = 0; t < g.tiles_m; ++t) g.rt_order[t] = (uint16_t)t;
 
-    hipStream_t s = (hipStream_t)stream;
     const hipError_t e = launch_gemm(g, cfg, P != nullptr, s);
     if (e != hipSuccess) return hip_error(e, "GEMM launch");
     return COMPASS_OK;

@@ -108,4 +108,21 @@ inline Plan plan_gemm(int M, int N, int K, bool partial, const PlanLimits &lim) 
     return best;
 }
 
+// Whether the few-row kernel (skinny_kernel: 16 columns per workgroup, K dealt
+// to its waves) beats the plan. Its stages take 0.06 us per 16 columns with up
+// to 16 rows, 0.015 more per further 16 rows, a third more when its workgroups
+// need several rounds (A's rows then compete with W for the caches); a plan
+// takes at least W's way in at 5.5 TB/s. 48 x 3072 x 8192: 25.2 us whole in
+// 64 x 64 tiles, 16.8 split in slices, 15.8 here; 8 x 12288 x 12288: 58.5
+// against 49.4; but 64 x 12288 x 12288: 74.4 against 101.
+inline bool skinny_faster(int M, int N, int K, bool partial, const Plan &pl, const PlanLimits &lim) {
+    if (M > kSkinnyRows) return false;
+    const int mt = (M + 15) / 16;
+    const long wgs = (N + 15) / 16, rounds = (wgs + lim.num_cu - 1) / lim.num_cu;
+    const double stage = (0.045 + 0.015 * mt) * (rounds > 1 ? 1.33 : 1.0);
+    const double skinny = rounds * (1.5 + (K + 63) / 64 * stage);
+    const double tiles = std::max(plan_cost(pl.cfg, pl.split, M, N, K, partial, lim), (double)N * K * 2 / 5.5e6);
+    return skinny < tiles;
+}
+
 }  // namespace compass

@@ -52,6 +52,7 @@
 namespace compass {
 
 hipError_t launch_gemm(const GemmParams &p, int cfg, bool rs, hipStream_t stream);
+hipError_t launch_skinny(const SkinnyParams &p, hipStream_t stream);
 hipError_t launch_join(const JoinParams &j, hipStream_t stream);
 hipError_t launch_mfma_probe(uint64_t *out, int grid, int iters, hipStream_t stream);
 
@@ -1800,6 +1801,19 @@ static int stage_resident_partials(const compass_problem *p, const Geometry &geo
     return COMPASS_OK;
 }
 
+// One GEMM kernel on the stream by `enqueue` (which returns its launch's
+// status), between HIP events when kernel timing is on.
+template <class F>
+static int timed_launch(hipStream_t s, F &&enqueue) {
+    Ctx &c = g_ctx;
+    const bool timed = c.timing && c.timed_count < Ctx::kTimed;
+    if (timed) (void)hipEventRecord(c.ev_begin[c.timed_count], s);
+    const hipError_t e = enqueue();
+    if (e != hipSuccess) return hip_fail(e, "GEMM launch");
+    if (timed) (void)hipEventRecord(c.ev_end[c.timed_count++], s);
+    return COMPASS_OK;
+}
+
 static int launch(const GemmParams &g0, int cfg, bool rs, hipStream_t s) {
     Ctx &c = g_ctx;
     GemmParams g = g0;
@@ -1812,12 +1826,7 @@ static int launch(const GemmParams &g0, int cfg, bool rs, hipStream_t s) {
         const uint64_t work = (uint64_t)work_items(g0);
         c.trace_used = std::min<uint64_t>(c.trace_cap, (uint64_t)c.trace_used + work);
     }
-    const bool timed = c.timing && c.timed_count < Ctx::kTimed;
-    if (timed) (void)hipEventRecord(c.ev_begin[c.timed_count], s);
-    const hipError_t e = launch_gemm(g, cfg, rs, s);
-    if (e != hipSuccess) return hip_fail(e, "GEMM launch");
-    if (timed) (void)hipEventRecord(c.ev_end[c.timed_count++], s);
-    return COMPASS_OK;
+    return timed_launch(s, [&] { return launch_gemm(g, cfg, rs, s); });
 }
 
 int op_kernel_times(double *us, int cap) {
@@ -2091,9 +2100,15 @@ int op_gemm(int M, int N, int K, const void *A, const void *W, void *C, const fl
                                                   "or the partial", K, N);
     int rc = begin();
     if (rc != COMPASS_OK) return rc;
+    const Plan pl = plan_launch(M, N, K, P != nullptr);
+    // (the few-row kernel has one tile shape and grid, and records no trace)
+    if (g_ctx.tile_override == 0 && g_ctx.grid_override == 0 && !g_ctx.tile_trace &&
+        skinny_faster(M, N, K, P != nullptr, pl, PlanLimits{g_ctx.num_cu, 0, 0}))
+        return timed_launch((hipStream_t)stream, [&] {
+            return launch_skinny({(const uint16_t *)A, (const uint16_t *)W, (uint16_t *)C, P, M, N, K}, (hipStream_t)stream);
+        });
     GemmParams g;
     init_params(g, g_ctx.epoch);
-    const Plan pl = plan_launch(M, N, K, P != nullptr);
     if ((rc = set_shape(g, pl.cfg, M, N, K, A, M, W, C, P)) != COMPASS_OK) return rc;
     g.gate = kGateNone;
     apply_plan(g, pl);

@@ -22,6 +22,13 @@ PLAN_SIZES = [
 ]
 
 
+# Few-row GEMMs: every row-block count, K from less than one stage to several
+# rounds of every wave, columns that end inside a workgroup's 16.
+FEW_ROW_SIZES = [(1, 8, 8, False), (16, 264, 520, True), (17, 2048, 4096, False), (32, 72, 72, True),
+                 (33, 1032, 1544, True), (48, 3072, 8192, False), (49, 776, 4104, True), (64, 264, 2056, False),
+                 (8, 12288, 1032, True)]
+
+
 def dev_bits(bits: np.ndarray, pinned: bool = False) -> torch.Tensor:
     """uint16 bf16 patterns -> int16 tensor on the GPU (or pinned host)."""
     t = torch.from_numpy(np.ascontiguousarray(bits).view(np.int16))

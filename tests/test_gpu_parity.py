@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 import oracle as O  # noqa: E402
 from paper_2609_10549_amd import compass as C  # noqa: E402
 from synth import make_ag_inputs, make_int_ag_inputs, make_int_rs_inputs, make_rs_inputs  # noqa: E402
-from tests.gpu_helpers import PLAN_SIZES, TOL, AGCase, RSCase, host_bits, host_f64, rel_err, dev_bits  # noqa: E402
+from tests.gpu_helpers import FEW_ROW_SIZES, PLAN_SIZES, TOL, AGCase, RSCase, host_bits, host_f64, rel_err, dev_bits  # noqa: E402
 
 FAST = C.links(200e9, 200e9)   # emulated link rates for functional tests
 
@@ -566,6 +566,22 @@ def test_every_tile_and_split_integer_exact(M, N, K, partial, cfg, split):
         fn(A, W, Cm, P)
         torch.cuda.synchronize()
         assert np.array_equal(host_bits(Cm), ref), fn.__name__
+
+
+@pytest.mark.parametrize("M,N,K,partial", FEW_ROW_SIZES)
+def test_few_rows_integer_exact(M, N, K, partial):
+    _say("few rows", M, N, K, partial)
+    inp = make_int_rs_inputs(M, N, K, 1, seed=M + N + K)
+    A, W = dev_bits(inp["A"]), dev_bits(inp["W"])
+    P = torch.from_numpy(inp["P_in"][0]).cuda() if partial else None
+    pin = inp["P_in"][0].astype(np.float64) if partial else np.zeros((M, N))
+    ref = O.f64_to_bf16_rne(O.gemm_rs(O.bf16_to_f64(inp["A"]), O.bf16_to_f64(inp["W"]), [pin], 1))
+    for fn in (C.compass_gemm, C.compass_gemm_noalloc):
+        Cm = torch.full((M + 1, N), 0x7FC0, dtype=torch.int16, device="cuda")   # one row more than C
+        fn(A, W, Cm[:M], P)
+        torch.cuda.synchronize()
+        assert np.array_equal(host_bits(Cm[:M]), ref), fn.__name__
+        assert (host_bits(Cm[M:]) == 0x7FC0).all(), fn.__name__
 
 
 # ------------------------------------------------------------ per-launch kernel timing

@@ -31,11 +31,14 @@ enum TileCfg : int {
     kTile128x64 = 5,     // 128 x 64,  DW 2,  64 KiB
     kTile128x64Deep = 6, // 128 x 64,  DW 4, 112 KiB
     kTile64 = 7,         //  64 x 64,  DW 4,  72 KiB
-    kTileCfgs = 8,
+    kTile192 = 8,        // 192 x 192, DW 2, 120 KiB
+    kTile128x192 = 9,    // 128 x 192, DW 3, 136 KiB
+    kTileCfgs = 10,
 };
 struct TileShape { int rows, cols, wg_per_cu; };
 constexpr TileShape kTileShapes[kTileCfgs] = {{256, 256, 1}, {128, 128, 2}, {256, 192, 1}, {256, 128, 1},
-                                              {128, 128, 1}, {128, 64, 2},  {128, 64, 1},  {64, 64, 2}};
+                                              {128, 128, 1}, {128, 64, 2},  {128, 64, 1},  {64, 64, 2},
+                                              {192, 192, 1}, {128, 192, 1}};
 inline int tile_rows(int cfg) { return kTileShapes[cfg].rows; }
 inline int tile_cols(int cfg) { return kTileShapes[cfg].cols; }
 inline int tile_wg_per_cu(int cfg) { return kTileShapes[cfg].wg_per_cu; }

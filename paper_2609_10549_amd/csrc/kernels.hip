@@ -602,7 +602,7 @@ void gemm_kernel(const GemmParams p) {
                 auto finish_split = [&](auto b_const, auto s_const) {
                     constexpr int S = decltype(s_const)::value;
                     constexpr int NP = FM * FN / 2;   // pairs (mi, 2 nj), (mi, 2 nj + 1)
-                    constexpr int B = decltype(b_const)::value < NP ? decltype(b_const)::value : NP;
+                    constexpr int WANT = decltype(b_const)::value, B = NP % WANT == 0 ? WANT : 2;
                     static_assert(NP % B == 0, "whole batches");
 #pragma unroll 1
                     for (int u0 = 0; u0 < NP; u0 += B) {
@@ -1001,6 +1001,8 @@ hipError_t launch_gemm(const GemmParams &p, int cfg, bool rs, hipStream_t stream
     case kTile128x64: launch_tile<128, 64, 2>(p, rs, stream); break;
     case kTile128x64Deep: launch_tile<128, 64, 4>(p, rs, stream); break;
     case kTile64: launch_tile<64, 64, 4>(p, rs, stream); break;
+    case kTile192: launch_tile<192, 192, 2>(p, rs, stream); break;
+    case kTile128x192: launch_tile<128, 192, 3>(p, rs, stream); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();

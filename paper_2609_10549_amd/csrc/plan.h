@@ -40,6 +40,8 @@ constexpr TileCost kTileCosts[kTileCfgs] = {
     {0.319f, 0.768f, 1.4f, 1.50f},   // 128 x 64, two per CU
     {0.205f, 0.293f, 2.2f, 1.65f},   // 128 x 64 deep
     {0.137f, 0.418f, 2.8f, 1.35f},   // 64 x 64, two per CU
+    {0.586f, 0.830f, 5.3f, 1.25f},   // 192 x 192
+    {0.440f, 0.630f, 4.0f, 1.40f},   // 128 x 192
 };
 
 inline int slices_of(int K, int split, int *kslice) {
@@ -60,7 +62,7 @@ inline double plan_cost(int cfg, int split, int M, int N, int K, bool partial, c
     // the partial's read, and, split, the completing slice's wait for the
     // partial tiles' way through memory (uncached) and its sums over them
     const double edge = tc.edge + (partial ? 6.0 * area * ts.wg_per_cu / 65536 : 0.0) +
-                        (sp > 1 ? (1.5 + sp * area * 4 / 65e3) * (items > lim.num_cu ? ts.wg_per_cu : 1) : 0.0);
+                        (sp > 1 ? (2.5 + sp * area * 4 / 65e3) * (items > lim.num_cu ? ts.wg_per_cu : 1) : 0.0);
     const long rounds = items / slots, rest = items % slots;
     double t = rounds * (stages * tc.full + edge);
     if (rest) {
@@ -105,6 +107,30 @@ inline Plan plan_gemm(int M, int N, int K, bool partial, const PlanLimits &lim) 
                 best = {cfg, slices_of(K, sp, &kslice)};
             }
         }
+    return best;
+}
+
+// Tile of a fused operator so small that tiles of at most 128 x 128 fit one
+// round of workgroups; -1 when no such tile's do. Every tile then starts with
+// the launch, and what follows the last arrival is one tile, so the estimate's
+// cheapest is the shortest tail: 512 x 1024 x 512 over two ranks 25.4 us in
+// 128 x 128 tiles (32 CUs busy), 22.0 in 64 x 64. (Larger tiles in one round
+// wait for more of the arrivals and leave a longer tail: the MLP fc1 218 us in
+// 256 x 256 tiles, 190 in two rounds of 256 x 128.)
+inline int plan_one_round(int M, int N, int K, bool partial, const PlanLimits &lim) {
+    int best = -1;
+    double tb = 1e30;
+    for (int cfg = 0; cfg < kTileCfgs; ++cfg) {
+        const TileShape &ts = kTileShapes[cfg];
+        const long tm = (M + ts.rows - 1) / ts.rows, tiles = tm * ((N + ts.cols - 1) / ts.cols);
+        const long slots = lim.slots_override > 0 ? lim.slots_override : (long)lim.num_cu * ts.wg_per_cu;
+        if (tm > kMaxRowTiles || tiles > slots || ts.rows > 128 || ts.cols > 128) continue;
+        const double t = plan_cost(cfg, 1, M, N, K, partial, lim);
+        if (t < tb) {
+            tb = t;
+            best = cfg;
+        }
+    }
     return best;
 }
 

@@ -1180,15 +1180,19 @@ static void init_params(GemmParams &g, uint32_t epoch) {
 }
 
 // Tile of a fused operator (prow: rows of its smallest partition).
-static int pick_tile(int M, int N, int prow, double lam_est, bool rs) {
+static int pick_tile(int M, int N, int K, int prow, double lam_est, bool rs) {
     if (g_ctx.tile_override == 1) return kTile256;
     if (g_ctx.tile_override == 2) return kTile128;
+    const int small = plan_one_round(M, N, K, rs, PlanLimits{g_ctx.num_cu, g_ctx.grid_override, 0});
+    if (small >= 0) return small;
     // The fused AllGather needs several tiles per arriving partition; it
     // takes the larger (faster) tile when a partition spans whole 256-row
     // tiles and the GEMM is at least two waves of 256 x 256 tiles (the tiles
     // of the last arrivals then split K, see set_tail_split): on the GPT-3
     // AllGather (3 waves, 4 : 1 double ring, lambda ~ 1) 1156 us against
-    // 1361 us with 128 x 128 tiles, whose main loop runs slower per flop.
+    // 1361 us with 128 x 128 tiles, whose main loop runs slower per flop. With
+    // fewer, 256 x 128 where they fill every CU (the MLP fc1 189.7 against
+    // 192.7 us with 128 x 128).
     // The fused ReduceScatter takes 256 x 256 only when computation dominates
     // (estimated lambda >= 1) over at least two waves: with one workgroup per
     // CU its chunks finish in bursts of a whole wave and the sends of the last
@@ -1198,7 +1202,11 @@ static int pick_tile(int M, int N, int prow, double lam_est, bool rs) {
     const bool whole = prow >= 256 && prow % 256 == 0;
     const long cu = g_ctx.num_cu;
     if (rs) return whole && t256 >= 2 * cu && lam_est >= 1.0 ? kTile256 : kTile128;
-    return whole && t256 >= 2 * cu ? kTile256 : kTile128;
+    if (!whole) return kTile128;
+    if (t256 >= 2 * cu) return kTile256;
+    // (the tail split of 128 x 128 tiles, an option, needs those tiles)
+    if (g_ctx.tail_min_k[1] > 0) return kTile128;
+    return (long)((M + 255) / 256) * ((N + 127) / 128) >= cu ? kTile256x128 : kTile128;
 }
 
 // Rough comp/comm ratio of a fused operator, used only to pick its tile: the
@@ -1937,11 +1945,11 @@ int op_ag_gemm(const compass_problem *p, const compass_links *l, void *stream) {
     // (rate-proportional parts: a 256-row tile may span both parts of a
     // chunk and waits for the later one, which an AllGather tolerates)
     const double lam = lambda_estimate(p, geo, l);
-    const int cfg = pick_tile(p->M, p->N, geo.fb != 0.5 && geo.sub == 1 ? geo.rows : min_part_rows(geo), lam, false);
+    const int cfg = pick_tile(p->M, p->N, p->K, geo.fb != 0.5 && geo.sub == 1 ? geo.rows : min_part_rows(geo), lam, false);
     if ((rc = set_shape(g, cfg, p->M, p->N, p->K, p->gathered, p->M, p->W, p->C, nullptr)) != COMPASS_OK) return rc;
     // 256-row tiles: one row-tile group per partition, so that the dealing
     // and the tail split follow partitions
-    if (cfg == kTile256 && geo.sub == 1 && geo.fb == 0.5 && min_part_rows(geo) % 256 == 0)
+    if (tile_rows(cfg) == 256 && geo.sub == 1 && geo.fb == 0.5 && min_part_rows(geo) % 256 == 0)
         g.group_m = std::max(1, std::min(4, min_part_rows(geo) / 256));
     double arrive[2 * kMaxRanks];
     if ((rc = expected_arrivals(p, geo, l, resident_mask(p, geo), arrive)) != COMPASS_OK) return rc;
@@ -1970,7 +1978,7 @@ int op_gemm_rs(const compass_problem *p, const compass_links *l, void *stream) {
     if ((rc = rs_jobs(p, geo, l, epoch, 1, res, true, true, jobs)) != COMPASS_OK) return rc;
     GemmParams g;
     init_params(g, epoch);
-    const int cfg = pick_tile(p->M, p->N, min_part_rows(geo), lambda_estimate(p, geo, l), true);
+    const int cfg = pick_tile(p->M, p->N, p->K, min_part_rows(geo), lambda_estimate(p, geo, l), true);
     if ((rc = set_shape(g, cfg, p->M, p->N, p->K, p->A, p->M, p->W, p->C, p->partial_stage)) != COMPASS_OK) return rc;
     bool aliased = false;
     if ((rc = alias_resident_partials(g, p, geo, res, cfg, &aliased)) != COMPASS_OK) return rc;

@@ -15,10 +15,10 @@ TOL = 5e-3   # normwise relative error bound for bf16 outputs
 # and splits of odd counts. tests/test_decode_host.py holds the plan to these.
 PLAN_SIZES = [
     (4095, 3080, 328, False, 0, 1), (300, 3000, 72, False, 1, 1), (3000, 4992, 200, True, 1, 1),
-    (4090, 3064, 520, True, 2, 1), (3969, 1992, 1000, False, 3, 1), (2049, 1000, 2048, True, 4, 1),
+    (4090, 3064, 520, True, 2, 1), (2040, 4088, 2048, False, 3, 1), (3969, 1992, 1000, False, 8, 1), (2049, 1000, 2048, True, 4, 1),
     (65, 72, 200, False, 5, 1), (770, 2056, 4096, True, 6, 1), (129, 1032, 4104, True, 6, 5),
     (512, 512, 12288, False, 6, 8), (513, 1024, 520, False, 7, 1), (1000, 776, 4104, True, 7, 1),
-    (640, 2048, 4096, False, 4, 3), (1024, 3072, 8192, True, 3, 2),
+    (256, 3072, 8192, False, 4, 5), (1024, 3072, 8192, True, 9, 2),
 ]
 
 

@@ -176,10 +176,26 @@ def _addr(x) -> int | None:
     return x.data_ptr()
 
 
+_current_stream = None
+
+
+def _find_current_stream():
+    """A function giving the address of the current stream of the current
+    device. torch.cuda.current_stream() builds a Stream object on every call
+    (2 us, a fifth of a small GEMM's whole call); its raw form is used where
+    this torch has it."""
+    import torch
+    raw, dev = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+    if raw is None or dev is None or not torch.cuda.is_initialized():
+        return lambda: torch.cuda.current_stream().cuda_stream
+    global _current_stream
+    _current_stream = lambda: raw(dev())  # noqa: E731
+    return _current_stream
+
+
 def _stream(stream) -> int | None:
     if stream is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream
+        return (_current_stream or _find_current_stream())()
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
@@ -210,6 +226,8 @@ def _need(x, what: str, shape: tuple, elsize: int) -> None:
     from M, N, K and n, so a mismatch would send its copies and loads outside
     the tensor). Plain int addresses are the caller's responsibility."""
     if x is None or isinstance(x, int):
+        return
+    if x.shape == shape and x.element_size() == elsize and x.is_contiguous():
         return
     if _shape_of(x) != tuple(shape):
         raise ValueError(f"{what}: shape {_shape_of(x)}, expected {tuple(shape)}")
@@ -309,25 +327,25 @@ def compass_decomp_gemm(problem: Problem, d: int, lk: compass_links | None = Non
            "compass_decomp_gemm")
 
 
-def compass_gemm(A, W, C, P=None, stream=None) -> None:
+def _gemm_call(name: str, A, W, C, P, stream) -> None:
     M, K = A.shape
     N = W.shape[0]
     _need(A, "A", (M, K), 2)
     _need(W, "W", (N, K), 2)
     _need(C, "C", (M, N), 2)
-    _need(P, "P", (M, N), 4)
-    _check(lib().compass_gemm(M, N, K, _addr(A), _addr(W), _addr(C), _addr(P), _stream(stream)), "compass_gemm")
+    if P is not None:
+        _need(P, "P", (M, N), 4)
+    rc = getattr(_lib or lib(), name)(M, N, K, _addr(A), _addr(W), _addr(C), _addr(P), _stream(stream))
+    if rc < 0:
+        _check(rc, name)
+
+
+def compass_gemm(A, W, C, P=None, stream=None) -> None:
+    _gemm_call("compass_gemm", A, W, C, P, stream)
 
 
 def compass_gemm_noalloc(A, W, C, P=None, stream=None) -> None:
-    M, K = A.shape
-    N = W.shape[0]
-    _need(A, "A", (M, K), 2)
-    _need(W, "W", (N, K), 2)
-    _need(C, "C", (M, N), 2)
-    _need(P, "P", (M, N), 4)
-    _check(lib().compass_gemm_noalloc(M, N, K, _addr(A), _addr(W), _addr(C), _addr(P), _stream(stream)),
-           "compass_gemm_noalloc")
+    _gemm_call("compass_gemm_noalloc", A, W, C, P, stream)
 
 
 def compass_transfer(problem: Problem, lk: compass_links | None = None, stream=None) -> None:

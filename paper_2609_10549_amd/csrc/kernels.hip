@@ -266,7 +266,15 @@ __device__ __forceinline__ void read_slot(const char *fa, const char *fw, bf16x8
     }
 }
 
-// MFMAs [I0, I1) of a substep on (a, b) (block i: acc[i / FM][i % FM]), with
+// Block row of MFMA slot i (block column i / FM): down one column of blocks, up
+// the next, so that consecutive MFMAs always share an operand. The operand that
+// stays costs no switching in the matrix core, and power is what bounds these
+// GEMMs: 8192 x 6144 x 12288 845 -> 832 us, 8192 x 12288 x 6144 with partial
+// 906 -> 897 (going down every column before).
+template <int FM>
+constexpr int slot_row(int i) { return i / FM % 2 ? FM - 1 - i % FM : i % FM; }
+
+// MFMAs [I0, I1) of a substep on (a, b) (block acc[i / FM][slot_row(i)]), with
 // the next substep's fragment reads into (na, nb) spread over MFMA slots
 // [R0, R1) and loads [L0, L0 + LC) of one operand over slots [D0, D1), in
 // exactly this order: an LDS read and a global load each occupy a unit that
@@ -277,7 +285,8 @@ __device__ __forceinline__ void mfma_slots(f32x4 (&acc)[FN][FM], const bf16x8 (&
                                            bf16x8 (&na)[FM], bf16x8 (&nb)[FN], const char *fa, const char *fw,
                                            i32x4 rsrc, uint32_t lds, const uint32_t *off, uint32_t kc2) {
     if constexpr (I < I1) {
-        acc[I / FM][I % FM] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[I / FM], a[I % FM], acc[I / FM][I % FM], 0, 0, 0);
+        constexpr int NI = I / FM, MI = slot_row<FM>(I);
+        acc[NI][MI] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[NI], a[MI], acc[NI][MI], 0, 0, 0);
         read_slot<0, I, R0, R1, FM, FN>(fa, fw, na, nb);
 #pragma unroll
         for (int j = 0; j < LC; ++j)
@@ -466,12 +475,11 @@ void gemm_kernel(const GemmParams p) {
                 // accumulation registers: saying so here keeps every one of
                 // them in its own register around the loop (the compiler had
                 // MFMAs write a neighbouring one and moved up to 68 registers
-                // back per stage: 8192 x 6144 x 12288 855 against 811 us)
+                // back per stage: 8192 x 6144 x 12288 855 against 811 us);
+                // in the MFMAs' order
                 if constexpr (kAcc) {
 #pragma unroll
-                    for (int ni = 0; ni < FN; ++ni)
-#pragma unroll
-                        for (int mi = 0; mi < FM; ++mi) asm volatile("" : "+a"(acc[ni][mi]));
+                    for (int i = 0; i < NM; ++i) asm volatile("" : "+a"(acc[i / FM][slot_row<FM>(i)]));
                 }
                 mfma_slots<0, NM, 0, RE, 0, LA, 0, NM, FM, FN>(acc, a0, b0, a1, b1, ca + coff1, cw + coff1, rA, aF + wb,
                                                              offA, kcf);

@@ -360,7 +360,8 @@ int compass_sync(void);
                                        8192; 0 = never; at most 2^21); only while the
                                        operator's estimated comp / comm ratio (the GEMM
                                        at 1 PFLOP/s against the slower direction's
-                                       transfer) is below 2 */
+                                       transfer) is below 2 (1.75 from three waves of
+                                       tiles on) */
 #define COMPASS_OPT_TAIL_MIN_K_128 14 /* the same for 128 x 128 tiles (default 0 = never) */
 #define COMPASS_OPT_TAIL_SLICE_K 15 /* least K depth of a tail slice, a positive multiple
                                        of 64 (default 2048) */
@@ -369,7 +370,7 @@ int compass_sync(void);
                                        twice as many groups */
 #define COMPASS_OPT_HEAD_SPLIT  17 /* fused AllGather under the tail split's conditions
                                        (256 x 256 tiles, K from COMPASS_OPT_TAIL_MIN_K,
-                                       estimated comp / comm ratio below 2): 1 = the tiles
+                                       estimated comp / comm ratio below the same): 1 = the tiles
                                        of the leading row-tile groups whose partitions are
                                        all resident (the rank's own chunk) split K into at
                                        most 4 slices, as many as the workgroup slots over

@@ -142,7 +142,7 @@ inline int plan_one_round(int M, int N, int K, bool partial, const PlanLimits &l
 // 64 x 64 tiles, 16.8 split in slices, 15.8 here; 8 x 12288 x 12288: 58.5
 // against 49.4; but 64 x 12288 x 12288: 74.4 against 101.
 inline bool skinny_faster(int M, int N, int K, bool partial, const Plan &pl, const PlanLimits &lim) {
-    if (M > kSkinnyRows) return false;
+    if (M > kSkinnyRows || N > (1 << 24)) return false;   // (the latter: threads of one launch below 2^32)
     const int mt = (M + 15) / 16;
     const long wgs = (N + 15) / 16, rounds = (wgs + lim.num_cu - 1) / lim.num_cu;
     const double stage = (0.045 + 0.015 * mt) * (rounds > 1 ? 1.33 : 1.0);

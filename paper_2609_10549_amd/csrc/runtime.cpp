@@ -92,6 +92,7 @@ constexpr int kSplitWsTiles = 3;     // workspace: this many 256 x 256 fp32 part
 constexpr int kTailMinK = 8192;      // fused AllGather: split the tail's K from this depth on
 constexpr int kTailSliceK = 2048;    // ... into slices at least this deep, at most 4
 constexpr double kTailMaxLambda = 2.0;   // ... when the estimated comp / comm ratio is below this
+constexpr double kTailMaxLambdaLong = 1.75;   // ... for launches of three waves of tiles or more
 // host_words layout (pinned, coherent host memory): start word, error word,
 // done flags (kernel -> copy side), arrival flags (copy side -> kernel)
 constexpr int kHwStart = 0, kHwErr = 1, kHwDone = 64, kHwFlags = kHwDone + kMaxFlags;
@@ -1312,11 +1313,21 @@ static void apply_plan(GemmParams &g, const Plan &pl) {
 // AllGather, 4 : 1 ring: lambda ~ 0.7 split 1474 against 1616 us whole,
 // lambda ~ 1 1117 against 1185 us; lambda ~ 2 split 1091 against 1038 us,
 // links unpaced 1074 against 1024 us).
+//
+// With the main loop at 1.5 PFLOP/s (lambda still counts 1): 8192 x 8192 x
+// 8192, 4 waves, lambda 1.85: split 853 against 804 us whole, 1.50: 860 / 888;
+// 3 waves, 1.69: 948 / 973 (K 12288) and 665 / 656 (K 8192); 2 waves, 1.87:
+// 471 / 475, 1.97: 477 / 474. Hence the two limits.
+static bool split_pays(const GemmParams &g, double lam_est) {
+    const bool is_long = g.tiles_m * g.tiles_n >= 3 * g_ctx.num_cu;
+    return lam_est < (is_long ? kTailMaxLambdaLong : kTailMaxLambda);
+}
+
 static void set_tail_split(GemmParams &g, int cfg, double lam_est) {
     Ctx &c = g_ctx;
     const int min_k = c.tail_min_k[cfg == kTile256 ? 0 : 1];
     if (!(c.sched & kSchedSplitK) || !c.split_ws || g.ksplit > 1 || min_k <= 0 || g.K < min_k) return;
-    if (!(lam_est < kTailMaxLambda)) return;
+    if (!split_pays(g, lam_est)) return;
     const int groups = (g.tiles_m + g.group_m - 1) / g.group_m;
     const int tail_groups = c.tail_groups;
     if (groups < 2 * tail_groups || g.tiles_m % g.group_m) return;
@@ -1344,7 +1355,7 @@ static void set_head_split(GemmParams &g, int cfg, double lam_est, uint64_t resi
     Ctx &c = g_ctx;
     const int min_k = c.tail_min_k[cfg == kTile256 ? 0 : 1];
     if (!c.head_split || !(c.sched & kSchedSplitK) || !c.split_ws || min_k <= 0 || g.K < min_k) return;
-    if (!(lam_est < kTailMaxLambda) || !resident) return;
+    if (!split_pays(g, lam_est) || !resident) return;
     int rt = 0;   // leading row tiles of the ready order with every partition resident
     while (rt < g.tiles_m) {
         const int t = g.rt_order[rt];

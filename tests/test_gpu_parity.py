@@ -210,6 +210,36 @@ def test_ag_gemm_tail_split_integer_exact(rank, ring):
     assert np.array_equal(host_bits(case.C), ref)
 
 
+@pytest.mark.parametrize("slow,whole", [(99e9, False), (135e9, True)])
+def test_ag_gemm_tail_split_limit_of_long_launches(slow, whole):
+    # three waves of 256 x 256 tiles: the tail (and head) split up to an
+    # estimated comp / comm ratio of 1.75 (here 1.39 and 1.89); small integers,
+    # every fp32 sum exact, so torch's fp32 product is the reference
+    M, N, K, n = 8192, 6144, 8192, 8
+    _say("ag tail limit", slow)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(77)
+    A = torch.randint(-4, 5, (M, K), generator=g, device="cuda").to(torch.bfloat16)
+    W = torch.randint(-4, 5, (N, K), generator=g, device="cuda").to(torch.bfloat16)
+    rows = M // n
+    gathered = torch.zeros_like(A)
+    gathered[:rows] = A[:rows]
+    shards = [gathered[:rows]] + [A[q * rows:(q + 1) * rows].clone() for q in range(1, n)]
+    Cm = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+    prob = C.ag_problem(shards, gathered, W, Cm, 0, "double")
+    C.compass_set_option(C.OPT_TILE_TRACE, 8192)
+    try:
+        C.compass_ag_gemm(prob, C.links(4 * slow, slow))
+        C.compass_sync()
+        rec = C.compass_tile_trace(8192)
+    finally:
+        C.compass_set_option(C.OPT_TILE_TRACE, 0)
+    assert (len(rec) == 32 * 24) == whole, len(rec)
+    for r in range(0, M, 2048):
+        ref = torch.matmul(A[r:r + 2048].float(), W.float().t().contiguous())
+        assert torch.equal(Cm[r:r + 2048], ref.to(torch.bfloat16)), r
+
+
 def test_ag_gemm_tail_split_128_tiles_option_integer_exact():
     # the tail (and head) split for 128 x 128 tiles (off by default): the fc1
     # shape, the last row-tile group (8 row tiles, the last ring step's two

@@ -1,33 +1,35 @@
 // gfx950 kernels of the Compass hot path.
 //
-// gemm_kernel<BM, BN, RS, WT>: persistent bf16 GEMM, C = A * W^T with fp32
+// gemm_kernel<BM, BN, DW, RS, WT>: persistent bf16 GEMM, C = A * W^T with fp32
 // accumulation on the CDNA4 matrix cores (v_mfma_f32_16x16x32_bf16) and one
-// bf16 round-to-nearest-even store. Workgroups take BM x BN output tiles from
-// atomic ticket queues in the order the host chose (ring-arrival order for
-// TA-IntraFusion, Section III-B), and, depending on the gate mode, wait on the
-// per-partition arrival flags published for the copy engines before reading A
-// (AllGather) or before adding the incoming partial sum (ReduceScatter).
+// bf16 round-to-nearest-even store. Workgroups take BM x BN output tiles in
+// the order the host chose (ring-arrival order for TA-IntraFusion, Section
+// III-B) and, depending on the gate mode, wait on the per-partition arrival
+// flags published for the copy engines before reading A (AllGather) or before
+// adding the incoming partial sum (ReduceScatter).
 //
-// Tile distribution: the ready order of tiles is cut into super-blocks; queue
-// v (one per XCD: workgroups are dispatched round-robin over the 8 XCDs, so
-// workgroup b serves queue b % 8) takes super-blocks v, v + 8, ...; inside
-// the order, positions walk a group of row tiles before moving to the next
-// column tile, so the tiles one XCD holds at a time share A rows and W rows
-// in that XCD's L2.
+// Tile distribution: launches whose tiles do not wait for one another, and
+// fused ones of one round, take fixed positions (static_position). The others
+// take tickets from atomic queues: the ready order of tiles is cut into
+// super-blocks; queue v (one per XCD: workgroups are dispatched round-robin
+// over the 8 XCDs, so workgroup b serves queue b % 8) takes super-blocks v,
+// v + 8, ... Inside the order, positions walk a group of row tiles before
+// moving to the next column tile, so the tiles one XCD holds at a time share A
+// rows and W rows in that XCD's L2.
 //
 // Data path per tile: 4 waves split the tile 2 x 2; each wave holds
 // (BM/2) x (BN/2) fp32 accumulators as 16 x 16 MFMA blocks. A and W stream
 // through LDS in stages of K = 64 (rows of 128 bytes, whole cache lines per
-// load: the texture path's cost grows with the lines a load touches), three
-// buffers of A and two of W (all 160 KiB for a 256 x 256 tile), with
+// load: the texture path's cost grows with the lines a load touches), DW + 1
+// buffers of A and DW of W (with DW = 2 all 160 KiB for a 256 x 256 tile), with
 // buffer_load ... lds (no register staging; out-of-range rows or K columns
 // read as zero through the buffer bound). The 16-byte chunks of LDS row r are
 // XOR-permuted with (r >> 1) & 7, so a fragment read hits distinct banks.
 //
-// What bounds it: the matrix cores at the clock the chip's power allows
-// (1.4 - 1.55 GHz under this load, 2.4 GHz nominal), so what counts is cycles
-// lost to waits and energy per flop. 8192 x 6144 x 12288, 256 x 256 tiles,
-// each step against the one before it on one box:
+// What bounds it: the large tiles, the matrix cores at the clock the chip's
+// power allows (1.4 - 1.55 GHz under this load, 2.4 GHz nominal), so what
+// counts is energy per flop and cycles lost to waits. 8192 x 6144 x 12288,
+// 256 x 256 tiles, each step against the one before it on one box:
 //  - three A buffers in place of two (loads have 1 to 1.75 stages to land; one
 //    barrier per stage): 942 -> 925 us;
 //  - LDS reads and global loads one at a time between the MFMAs in place of
@@ -36,7 +38,13 @@
 //  - v_mfma_f32_16x16x32_bf16 in place of 32x32x16: half the accumulator
 //    traffic per flop (each accumulator is read and written once per 32 of K
 //    in place of 16), a higher clock and shorter stalls: 908 -> 834 us
-//    (1.48 PFLOP/s; stage time 1.46 -> 1.38 us).
+//    (1.48 PFLOP/s; stage time 1.46 -> 1.38 us);
+//  - consecutive MFMAs always sharing an operand (slot_row): 845 -> 832 us.
+// The small tiles are bound by the latency of a stage (barrier, LDS, loads),
+// for which DW = 3 or 4 keeps the loads of that many stages in flight: 48 rows
+// x 8192 x 3072 in 128 x 64 tiles, a stage 0.32 us with DW = 2, 0.205 with 4.
+//
+// skinny_kernel: the GEMM for at most 64 rows.
 //
 // join_kernel: one wave that (optionally) marks the start of a transfer job
 // and waits for a list of flags, putting the end of the copy side onto the

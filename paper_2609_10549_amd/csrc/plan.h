@@ -21,7 +21,6 @@ struct PlanLimits {
 };
 
 constexpr int kMinSliceK = 512;     // K depth of a slice at least
-constexpr int kFewTiles = 4;        // 128 x 128 tiles of the smallest launches
 
 // Microseconds on MI355X (bf16, N(0, 1) data), fitted to launches of 8 to 192
 // stages of K = 64: a stage on one workgroup with most of the chip idle
@@ -86,15 +85,6 @@ inline Plan plan_gemm(int M, int N, int K, bool partial, const PlanLimits &lim) 
         return ts.rows > 64 && K / split >= kMinSliceK && tiles <= kMaxSplitTiles && tiles * split <= slots &&
                (uint64_t)tiles * split * ts.rows * ts.cols * 4 <= lim.split_bytes;
     };
-    // the smallest launches: as many K slices as their depth holds. (256 x 256,
-    // K = 2560 to 4096; the estimate's differences there are below its error)
-    const long t128 = (long)((M + 127) / 128) * ((N + 127) / 128);
-    if (t128 <= kFewTiles && M > 128 && N > 128) {
-        int sp = std::min(kMaxSplit, std::max(1, K / kMinSliceK));
-        while (sp > 1 && !allowed(kTile128, sp)) --sp;
-        int kslice;
-        return {kTile128, slices_of(K, sp, &kslice)};
-    }
     Plan best{kTile128, 1};
     double tb = 1e30;
     for (int cfg = 0; cfg < kTileCfgs; ++cfg)

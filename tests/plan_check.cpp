@@ -1,8 +1,9 @@
 // Host check of the launch plan (plan.h) and of the fixed work positions
 // (kernel_params.h: static_position): over a grid of GEMM sizes, odd ones among
 // them, the plan's row tiles fit the row-tile table, a split fits one round of
-// workgroups, the split counters and the workspace, no slice is empty, and the
-// rounds of all workgroups take every work position once. The sizes given as
+// workgroups, the split counters and the workspace, no slice is empty, no plan
+// within these bounds has a lower estimate, and the rounds of all workgroups
+// take every work position once. The sizes given as
 // arguments ("M,N,K,partial,cfg,split") must get that tile and split.
 // Prints "ok <sizes>" or the first failure.
 #include <cstdio>
@@ -45,6 +46,18 @@ static bool check(int M, int N, int K, bool partial, const PlanLimits &lim, char
             (uint64_t)tiles * g.ksplit * ts.rows * ts.cols * 4 > lim.split_bytes) { std::sprintf(why, "split out of bounds"); return false; }
         if ((g.ksplit - 1) * g.kslice >= K || g.kslice % 64) { std::sprintf(why, "slice %d of K %d", g.kslice, K); return false; }
     }
+    const double cost = plan_cost(pl.cfg, pl.split, M, N, K, partial, lim);
+    for (int cfg = 0; cfg < kTileCfgs; ++cfg)
+        for (int sp = 1; sp <= kMaxSplit; ++sp) {
+            const TileShape &o = kTileShapes[cfg];
+            const long tm = (M + o.rows - 1) / o.rows, t = tm * ((N + o.cols - 1) / o.cols);
+            if (tm > kMaxRowTiles) continue;
+            if (sp > 1 && (o.rows <= 64 || K / sp < kMinSliceK || t > kMaxSplitTiles || t * sp > (long)lim.num_cu * o.wg_per_cu ||
+                           (uint64_t)t * sp * o.rows * o.cols * 4 > lim.split_bytes))
+                continue;
+            const double c = plan_cost(cfg, sp, M, N, K, partial, lim);
+            if (c < cost * (1 - 1e-9)) { std::sprintf(why, "plan %d/%d at %.2f us, %d/%d at %.2f", pl.cfg, pl.split, cost, cfg, sp, c); return false; }
+        }
     const int all = work_items(g);
     std::vector<char> seen(all, 0);
     for (int b = 0; b < g.grid; ++b)

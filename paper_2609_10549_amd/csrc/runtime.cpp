@@ -1184,7 +1184,10 @@ static void init_params(GemmParams &g, uint32_t epoch) {
 static int pick_tile(int M, int N, int K, int prow, double lam_est, bool rs) {
     if (g_ctx.tile_override == 1) return kTile256;
     if (g_ctx.tile_override == 2) return kTile128;
-    const int small = plan_one_round(M, N, K, rs, PlanLimits{g_ctx.num_cu, g_ctx.grid_override, 0});
+    // an AllGather deep enough for the tail split of 128 x 128 tiles (an
+    // option) takes those tiles, or 256 x 256
+    const bool tail_128 = !rs && g_ctx.tail_min_k[1] > 0 && K >= g_ctx.tail_min_k[1];
+    const int small = tail_128 ? -1 : plan_one_round(M, N, K, rs, PlanLimits{g_ctx.num_cu, g_ctx.grid_override, 0});
     if (small >= 0) return small;
     // The fused AllGather needs several tiles per arriving partition; it
     // takes the larger (faster) tile when a partition spans whole 256-row
@@ -1205,8 +1208,7 @@ static int pick_tile(int M, int N, int K, int prow, double lam_est, bool rs) {
     if (rs) return whole && t256 >= 2 * cu && lam_est >= 1.0 ? kTile256 : kTile128;
     if (!whole) return kTile128;
     if (t256 >= 2 * cu) return kTile256;
-    // (the tail split of 128 x 128 tiles, an option, needs those tiles)
-    if (g_ctx.tail_min_k[1] > 0) return kTile128;
+    if (tail_128) return kTile128;
     return (long)((M + 255) / 256) * ((N + 127) / 128) >= cu ? kTile256x128 : kTile128;
 }
 
@@ -1323,9 +1325,16 @@ static bool split_pays(const GemmParams &g, double lam_est) {
     return lam_est < (is_long ? kTailMaxLambdaLong : kTailMaxLambda);
 }
 
+// Least depth of K for the head and tail split of tiles of `cfg` (0: none).
+// The other tiles never split a fused AllGather (the smallest one's kernel
+// holds no split).
+static int split_min_k(int cfg) {
+    return cfg == kTile256 ? g_ctx.tail_min_k[0] : cfg == kTile128 ? g_ctx.tail_min_k[1] : 0;
+}
+
 static void set_tail_split(GemmParams &g, int cfg, double lam_est) {
     Ctx &c = g_ctx;
-    const int min_k = c.tail_min_k[cfg == kTile256 ? 0 : 1];
+    const int min_k = split_min_k(cfg);
     if (!(c.sched & kSchedSplitK) || !c.split_ws || g.ksplit > 1 || min_k <= 0 || g.K < min_k) return;
     if (!split_pays(g, lam_est)) return;
     const int groups = (g.tiles_m + g.group_m - 1) / g.group_m;
@@ -1353,7 +1362,7 @@ static void set_tail_split(GemmParams &g, int cfg, double lam_est) {
 // done sooner; the workspace holds both the head's and the tail's partials.
 static void set_head_split(GemmParams &g, int cfg, double lam_est, uint64_t resident) {
     Ctx &c = g_ctx;
-    const int min_k = c.tail_min_k[cfg == kTile256 ? 0 : 1];
+    const int min_k = split_min_k(cfg);
     if (!c.head_split || !(c.sched & kSchedSplitK) || !c.split_ws || min_k <= 0 || g.K < min_k) return;
     if (!split_pays(g, lam_est) || !resident) return;
     int rt = 0;   // leading row tiles of the ready order with every partition resident

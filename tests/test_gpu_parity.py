@@ -272,6 +272,33 @@ def test_ag_gemm_tail_split_128_tiles_option_integer_exact():
     assert np.array_equal(host_bits(case.C), ref)
 
 
+@pytest.mark.parametrize("min_k,records", [(8192, 64 * 2 + 2 * 16 * 3 + 16 * 3), (16384, 0)])
+def test_ag_gemm_tail_split_128_tiles_option_on_small_launches(min_k, records):
+    # a launch whose small tiles fit one round of workgroups: with the option
+    # on it takes 64 x 2 tiles of 128 x 128, the last two groups' (8 row tiles
+    # each) and the rank's own chunk's (8 row tiles) in 4 K slices; below the
+    # option's depth it runs the tiles of a launch without it
+    M, N, K, n = 8192, 256, 8192, 8
+    inp = make_int_ag_inputs(M, N, K, n, seed=42)
+    ref = O.f64_to_bf16_rne(O.ag_gemm([O.bf16_to_f64(s) for s in inp["shards"]], O.bf16_to_f64(inp["W"])))
+    case = AGCase(inp, 2, "double")
+    counts = {}
+    try:
+        for opt in (0, min_k):
+            _say("ag tail split 128, small", opt)
+            case.C.fill_(0x7FC0)
+            C.compass_set_option(C.OPT_TAIL_MIN_K_128, opt)
+            C.compass_set_option(C.OPT_TILE_TRACE, 8192)
+            C.compass_ag_gemm(case.problem, FAST)
+            C.compass_sync()
+            counts[opt] = len(C.compass_tile_trace(8192))
+            assert np.array_equal(host_bits(case.C), ref), opt
+    finally:
+        C.compass_set_option(C.OPT_TILE_TRACE, 0)
+        C.compass_set_option(C.OPT_TAIL_MIN_K_128, 0)
+    assert counts[min_k] == (records or counts[0])
+
+
 def test_ag_gemm_config1_all_ranks():
     # AllGather-GEMM, TP=2: shards 256x512 U[-1,1], B 512x1024, single ring
     inp = make_ag_inputs(512, 1024, 512, 2, seed=1, dist_a=("uniform", -1.0, 1.0), dist_w=("uniform", -1.0, 1.0))

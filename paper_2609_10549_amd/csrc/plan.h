@@ -14,10 +14,15 @@ struct Plan {
 };
 
 // What may be split: the workspace's fp32 partial tiles, in bytes (0: nothing).
+// A launch that reads part of its partial from other buffers can do so when
+// the rows of its tiles divide `row_step`; with other tiles those rows are
+// copied first, which takes `staging_us`.
 struct PlanLimits {
     int num_cu;
     int slots_override;     // workgroups per launch (0: as many as the CUs hold)
     uint64_t split_bytes;
+    int row_step = 0;
+    double staging_us = 0.0;
 };
 
 constexpr int kMinSliceK = 512;     // K depth of a slice at least
@@ -71,7 +76,7 @@ inline double plan_cost(int cfg, int split, int M, int N, int K, bool partial, c
         const double x = rest > lim.num_cu ? std::max(0.9, (double)rest / slots) : (double)rest / slots;
         t += stages * (tc.alone + (tc.full - tc.alone) * x * x) + edge;
     }
-    return t;
+    return lim.row_step % ts.rows ? t + lim.staging_us : t;
 }
 
 inline Plan plan_gemm(int M, int N, int K, bool partial, const PlanLimits &lim) {

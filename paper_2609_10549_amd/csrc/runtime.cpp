@@ -40,6 +40,7 @@
 #include <deque>
 #include <memory>
 #include <mutex>
+#include <numeric>
 #include <string>
 #include <thread>
 #include <vector>
@@ -1273,10 +1274,14 @@ static int set_shape(GemmParams &g, int cfg, int M, int N, int K, const void *A,
 // that restrict it: COMPASS_OPT_TILE (that tile, as many slices as fill its
 // slots, each at least kMinSliceK deep), COMPASS_OPT_GRID and the split bit of
 // COMPASS_OPT_SCHED.
-static Plan plan_launch(int M, int N, int K, bool partial) {
+// `base`: further limits (its rows and staging time).
+static Plan plan_launch(int M, int N, int K, bool partial, const PlanLimits &base = {}) {
     Ctx &c = g_ctx;
     const bool may_split = (c.sched & kSchedSplitK) && c.split_ws;
-    const PlanLimits lim{c.num_cu, c.grid_override, may_split ? (uint64_t)c.split_ws_bytes : 0};
+    PlanLimits lim = base;
+    lim.num_cu = c.num_cu;
+    lim.slots_override = c.grid_override;
+    lim.split_bytes = may_split ? (uint64_t)c.split_ws_bytes : 0;
     if (c.tile_override == 0) return plan_gemm(M, N, K, partial, lim);
     const int cfg = c.tile_override == 1 ? kTile256 : kTile128;
     const long tiles = (long)((M + tile_rows(cfg) - 1) / tile_rows(cfg)) * ((N + tile_cols(cfg) - 1) / tile_cols(cfg));
@@ -1759,20 +1764,14 @@ static int stage_local_shard(const compass_problem *p, const Geometry &geo, hipS
     return e == hipSuccess ? COMPASS_OK : hip_fail(e, "local shard copy");
 }
 
-// The first step's partials (the resident partitions) read by the kernel
-// straight from the caller's buffers, with no staging copy: per chunk, the
-// rows its resident partitions cover, contiguous in the chunk, become an
-// aliased row range of the landing buffer (GemmParams::palt) whose partial
-// the epilogue reads from partial_src[c]. Needs device memory 16-byte
-// aligned, the identity row map, range ends on tile boundaries (no tile
-// reads two buffers) and at most two ranges; *aliased false otherwise, and
-// the caller stages them.
-static int alias_resident_partials(GemmParams &g, const compass_problem *p, const Geometry &geo, uint64_t resident,
-                                   int cfg, bool *aliased) {
-    *aliased = false;
-    if (g.piece != 0) return COMPASS_OK;
-    const int bm = tile_rows(cfg);
-    int lo[2], hi[2], chunk[2], k = 0;
+// Row ranges of the landing buffer that hold the first step's partials (the
+// resident partitions): per chunk, the rows its resident partitions cover.
+// False when there are more than two or one is not contiguous, or a source is
+// not 16-byte aligned (the epilogue reads the partial 16 bytes at a time).
+struct ResidentRows { int k, lo[2], hi[2], chunk[2]; };
+
+static bool resident_rows(const compass_problem *p, const Geometry &geo, uint64_t resident, ResidentRows *r) {
+    r->k = 0;
     for (int c = 0; c < p->n; ++c) {
         int a = geo.rows, b = -1, rows = 0;
         for (int q = 0; q < geo.P; ++q) {
@@ -1784,27 +1783,65 @@ static int alias_resident_partials(GemmParams &g, const compass_problem *p, cons
             rows += cnt;
         }
         if (b < 0) continue;
-        const int plo = c * geo.rows + a, phi = c * geo.rows + b;
-        if (k == 2 || rows != b - a || plo % bm || (phi % bm && phi != p->M)) return COMPASS_OK;
-        // (the epilogue reads the partial 16 bytes at a time)
-        if ((uintptr_t)p->partial_src[c] % 16) return COMPASS_OK;
+        if (r->k == 2 || rows != b - a || (uintptr_t)p->partial_src[c] % 16) return false;
+        r->lo[r->k] = c * geo.rows + a;
+        r->hi[r->k] = c * geo.rows + b;
+        r->chunk[r->k++] = c;
+    }
+    return true;
+}
+
+// The first step's partials read by the kernel straight from the caller's
+// buffers, with no staging copy: their row ranges become aliased ranges
+// (GemmParams::palt) whose partial the epilogue reads from partial_src[c].
+// Needs device memory, the identity row map and range ends on tile boundaries
+// (no tile reads two buffers); *aliased false otherwise, and the caller
+// stages them.
+static int alias_resident_partials(GemmParams &g, const compass_problem *p, const Geometry &geo, uint64_t resident,
+                                   int cfg, bool *aliased) {
+    *aliased = false;
+    ResidentRows r;
+    if (g.piece != 0 || !resident_rows(p, geo, resident, &r)) return COMPASS_OK;
+    const int bm = tile_rows(cfg);
+    for (int i = 0; i < r.k; ++i) {
+        if (r.lo[i] % bm || (r.hi[i] % bm && r.hi[i] != p->M)) return COMPASS_OK;
         hsa_agent_t owner;
-        const int rc = agent_of(p->partial_src[c], &owner);
+        const int rc = agent_of(p->partial_src[r.chunk[i]], &owner);
         if (rc != COMPASS_OK) return rc;
         if (owner.handle != g_ctx.gpu.handle) return COMPASS_OK;
-        lo[k] = plo;
-        hi[k] = phi;
-        chunk[k] = c;
-        ++k;
     }
-    for (int i = 0; i < k; ++i) {
-        g.palt[i] = (const float *)((const char *)p->partial_src[chunk[i]] + (size_t)(lo[i] - chunk[i] * geo.rows) *
-                                                                               (size_t)p->N * 4);
-        g.palt_lo[i] = lo[i];
-        g.palt_hi[i] = hi[i];
+    for (int i = 0; i < r.k; ++i) {
+        g.palt[i] = (const float *)((const char *)p->partial_src[r.chunk[i]] +
+                                    (size_t)(r.lo[i] - r.chunk[i] * geo.rows) * (size_t)p->N * 4);
+        g.palt_lo[i] = r.lo[i];
+        g.palt_hi[i] = r.hi[i];
     }
     *aliased = true;
     return COMPASS_OK;
+}
+
+// For the plan of a launch that calls alias_resident_partials: what the tile's
+// rows have to divide for it, and the time of the copies otherwise (one per
+// range at least; a copy on the stream takes 3.3 us and 4.4 TB/s of its bytes: 3.6 us
+// for 3.1 MB, 14.8 for 50.3). Both 0 where the copies are made, or not needed,
+// with any tile.
+static void staging_limits(const compass_problem *p, const Geometry &geo, uint64_t resident, PlanLimits *lim) {
+    ResidentRows r;
+    if (!resident_rows(p, geo, resident, &r)) return;
+    int step = 0;
+    double us = 0.0;
+    for (int i = 0; i < r.k; ++i) {
+        hsa_agent_t owner;
+        if (agent_of(p->partial_src[r.chunk[i]], &owner) != COMPASS_OK || owner.handle != g_ctx.gpu.handle) return;
+        step = std::gcd(step, r.lo[i]);
+        if (r.hi[i] != p->M) step = std::gcd(step, r.hi[i]);
+        const char *src = (const char *)p->partial_src[r.chunk[i]] +
+                          (size_t)(r.lo[i] - r.chunk[i] * geo.rows) * (size_t)p->N * 4;
+        if (src == (const char *)p->partial_stage + (size_t)r.lo[i] * (size_t)p->N * 4) continue;   // in place
+        us += 3.3 + (double)(r.hi[i] - r.lo[i]) * p->N * 4 / 4.4e6;
+    }
+    lim->row_step = step;
+    lim->staging_us = us;
 }
 
 // The partials of the resident partitions, for each of the d sub-operators
@@ -2187,7 +2224,9 @@ int op_sequential(const compass_problem *p, const compass_links *l, void *stream
     if ((rc = rs_jobs(p, geo, l, epoch, 1, res, false, true, jobs)) != COMPASS_OK) return rc;
     GemmParams g;
     init_params(g, epoch);
-    const Plan pl = plan_launch(p->M, p->N, p->K, true);
+    PlanLimits stage{};
+    staging_limits(p, geo, res, &stage);
+    const Plan pl = plan_launch(p->M, p->N, p->K, true, stage);
     const int cfg = pl.cfg;
     if ((rc = set_shape(g, cfg, p->M, p->N, p->K, p->A, p->M, p->W, p->C, p->partial_stage)) != COMPASS_OK) return rc;
     bool aliased = false;

@@ -46,7 +46,14 @@ static bool check(int M, int N, int K, bool partial, const PlanLimits &lim, char
             (uint64_t)tiles * g.ksplit * ts.rows * ts.cols * 4 > lim.split_bytes) { std::sprintf(why, "split out of bounds"); return false; }
         if ((g.ksplit - 1) * g.kslice >= K || g.kslice % 64) { std::sprintf(why, "slice %d of K %d", g.kslice, K); return false; }
     }
-    const double cost = plan_cost(pl.cfg, pl.split, M, N, K, partial, lim);
+    // the staging copies on top of the estimate for tiles they cannot do without
+    PlanLimits bare = lim;
+    bare.row_step = 0;
+    auto cost_of = [&](int cfg, int sp) {
+        return plan_cost(cfg, sp, M, N, K, partial, bare) +
+               (lim.row_step && lim.row_step % kTileShapes[cfg].rows ? lim.staging_us : 0.0);
+    };
+    const double cost = cost_of(pl.cfg, pl.split);
     for (int cfg = 0; cfg < kTileCfgs; ++cfg)
         for (int sp = 1; sp <= kMaxSplit; ++sp) {
             const TileShape &o = kTileShapes[cfg];
@@ -55,7 +62,7 @@ static bool check(int M, int N, int K, bool partial, const PlanLimits &lim, char
             if (sp > 1 && (o.rows <= 64 || K / sp < kMinSliceK || t > kMaxSplitTiles || t * sp > (long)lim.num_cu * o.wg_per_cu ||
                            (uint64_t)t * sp * o.rows * o.cols * 4 > lim.split_bytes))
                 continue;
-            const double c = plan_cost(cfg, sp, M, N, K, partial, lim);
+            const double c = cost_of(cfg, sp);
             if (c < cost * (1 - 1e-9)) { std::sprintf(why, "plan %d/%d at %.2f us, %d/%d at %.2f", pl.cfg, pl.split, cost, cfg, sp, c); return false; }
         }
     const int all = work_items(g);
@@ -72,7 +79,8 @@ static bool check(int M, int N, int K, bool partial, const PlanLimits &lim, char
 }
 
 int main(int argc, char **argv) {
-    const PlanLimits split{256, 0, 3ull * 256 * 256 * 256 * 4}, whole{256, 0, 0}, small{4, 0, 3ull * 4 * 256 * 256 * 4};
+    const PlanLimits split{256, 0, 3ull * 256 * 256 * 256 * 4}, whole{256, 0, 0}, small{4, 0, 3ull * 4 * 256 * 256 * 4},
+                     stage128{256, 0, split.split_bytes, 128, 8.0}, stage192{256, 0, split.split_bytes, 192, 8.0};
     char why[256];
     int count = 0;
     const int Ms[] = {1, 15, 64, 65, 127, 129, 257, 640, 1000, 2049, 4096, 8191, 32768, 32769, 65536};
@@ -82,7 +90,7 @@ int main(int argc, char **argv) {
         for (int N : Ns)
             for (int K : Ks)
                 for (int p = 0; p < 2; ++p)
-                    for (const PlanLimits &lim : {split, whole, small}) {
+                    for (const PlanLimits &lim : {split, whole, small, stage128, stage192}) {
                         ++count;
                         if (!check(M, N, K, p, lim, why)) {
                             std::printf("FAIL %d x %d x %d partial %d cus %d: %s\n", M, N, K, p, lim.num_cu, why);

@@ -512,6 +512,42 @@ def test_sequential_ag_and_rs():
     assert rel_err(host_f64(rcase.C), rcase.reference()) < TOL
 
 
+@pytest.mark.parametrize("n,misaligned", [(16, False), (32, False), (16, True)])
+def test_sequential_rs_reads_first_step_partials_in_place(n, misaligned):
+    # partitions of 128 (n = 16) and 64 rows (n = 32), in a launch whose tiles
+    # would have 256 rows by the GEMM alone: where a tile of 128 rows costs less
+    # than the staging copies the partials are read in place and the landing
+    # buffer's own rows stay as they were (NaN); 64-row tiles cost more, and a
+    # misaligned source is always staged
+    M, N, K, r = 4096, 2048, 2048, 3
+    inp = make_int_rs_inputs(M, N, K, n, seed=64)
+    ref = O.f64_to_bf16_rne(O.gemm_rs(O.bf16_to_f64(inp["A"]), O.bf16_to_f64(inp["W"]),
+                                      [p.astype(np.float64) for p in inp["P_in"]], n))
+    case = RSCase(inp, r, "double")
+    rows = M // n
+    if misaligned:
+        keep = [torch.empty(rows * N + 4, dtype=torch.float32, device="cuda") for _ in range(n)]
+        for c in range(n):
+            keep[c][1:1 + rows * N].copy_(case.partials[c].reshape(-1))
+        case.partials = [keep[c][1:1 + rows * N].view(rows, N) for c in range(n)]
+        case.problem = C.rs_problem(case.A, case.W, case.partials, case.stage, case.C, case.send, r, "double")
+    case.stage.fill_(float("nan"))
+    torch.cuda.synchronize()
+    _say("sequential rs in place", n, misaligned)
+    C.compass_transfer(case.problem, FAST)
+    C.compass_sync()
+    first = torch.isnan(case.stage).all(dim=1)   # the first step's rows: resident, not transferred
+    assert int(first.sum()) == rows
+    C.compass_sequential(case.problem, FAST)
+    C.compass_sync()
+    assert np.array_equal(host_bits(case.C), ref)
+    in_place = n == 16 and not misaligned
+    assert bool(torch.isnan(case.stage[first]).all()) == in_place
+    for q in range(n):
+        if q != r:
+            assert np.array_equal(host_bits(case.send[q]), ref[q * rows:(q + 1) * rows]), f"send {q}"
+
+
 # ------------------------------------------------------------ failure handling
 def test_never_arriving_partition_times_out_then_recovers():
     n = 4

@@ -656,10 +656,10 @@ void gemm_kernel(const GemmParams p) {
                         }
                     }
                 };
-                // The host splits a tile into 2 to 8 slices (more only through
-                // kMaxSplit): each count has its own branch-free instance, with
-                // batches that keep the loads within the registers the main loop
-                // leaves.
+                // The host splits a tile into 2 to kMaxSplit slices: each count
+                // has its own branch-free instance, with batches that keep the
+                // loads within the registers the main loop leaves.
+                static_assert(kMaxSplit == 8, "one instance per slice count");
                 using std::integral_constant;
                 switch (ns) {
                 case 2: finish_split(integral_constant<int, 4>{}, integral_constant<int, 2>{}); break;
@@ -668,6 +668,7 @@ void gemm_kernel(const GemmParams p) {
                 case 5: finish_split(integral_constant<int, 2>{}, integral_constant<int, 5>{}); break;
                 case 6: finish_split(integral_constant<int, 2>{}, integral_constant<int, 6>{}); break;
                 case 7: finish_split(integral_constant<int, 2>{}, integral_constant<int, 7>{}); break;
+                case 8:
                 default: finish_split(integral_constant<int, 2>{}, integral_constant<int, 8>{}); break;
                 }
             } else {

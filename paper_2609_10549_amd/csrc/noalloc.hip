@@ -102,8 +102,6 @@ int op_gemm_noalloc(int M, int N, int K, const void *A, const void *W, void *C, 
     g.tiles_n = (N + bn - 1) / bn;
     const int total = g.tiles_m * g.tiles_n;
     g.grid = std::max(1, std::min(total, num_cu * tile_wg_per_cu(cfg)));
-    g.nq = g.grid >= kMaxQueues ? kMaxQueues : 1;
-    g.q_size = std::max(1, g.grid / g.nq);
     g.group_m = bm == 256 ? 4 : 8;
     g.fixed = 1;
     g.ksplit = 1;

@@ -10,15 +10,42 @@ from paper_2609_10549_amd import compass as C
 
 TOL = 5e-3   # normwise relative error bound for bf16 outputs
 
+# Rows and columns of kernel_params.h's tile configurations.
+TILE_SHAPES = [(256, 256), (128, 128), (256, 192), (256, 128), (128, 128), (128, 64), (128, 64), (64, 64), (192, 192), (128, 192)]
+
 # (M, N, K, partial, tile configuration, K slices): plain GEMMs that reach
-# every tile of kernel_params.h's TileCfg, with edges inside tiles and stages,
-# and splits of odd counts. tests/test_decode_host.py holds the plan to these.
+# every tile of kernel_params.h's TileCfg whole, with and without a partial,
+# and every tile that splits K in an even and an odd count, with edges inside
+# tiles and stages. tests/test_decode_host.py holds the plan to these.
 PLAN_SIZES = [
     (4095, 3080, 328, False, 0, 1), (300, 3000, 72, False, 1, 1), (3000, 4992, 200, True, 1, 1),
     (4090, 3064, 520, True, 2, 1), (2040, 4088, 2048, False, 3, 1), (3969, 1992, 1000, False, 8, 1), (2049, 1000, 2048, True, 4, 1),
     (65, 72, 200, False, 5, 1), (770, 2056, 4096, True, 6, 1), (129, 1032, 4104, True, 6, 5),
     (512, 512, 12288, False, 6, 8), (513, 1024, 520, False, 7, 1), (1000, 776, 4104, True, 7, 1),
     (256, 3072, 8192, False, 4, 5), (1024, 3072, 8192, True, 9, 2),
+    (2500, 4912, 264, True, 0, 1), (2500, 2512, 3080, False, 0, 2), (2500, 1792, 4104, True, 0, 3),
+    (1300, 936, 3080, False, 1, 2), (1537, 656, 2056, False, 1, 3),
+    (2500, 3472, 264, False, 2, 1), (3000, 1552, 4104, True, 2, 2), (2500, 1160, 5128, False, 2, 3),
+    (3000, 2032, 1032, True, 3, 1), (2500, 1160, 4104, False, 3, 2), (2500, 824, 4104, True, 3, 3),
+    (3000, 656, 2048, False, 4, 1), (1537, 992, 3080, True, 4, 2), (2500, 1552, 136, True, 5, 1), (1537, 656, 520, False, 6, 1),
+    (2500, 3232, 136, True, 8, 1), (2500, 1552, 3080, True, 8, 2), (1537, 1440, 4104, False, 8, 3), (129, 6832, 12288, True, 8, 6),
+    (2500, 1552, 520, False, 9, 1), (1300, 2992, 264, True, 9, 1), (1537, 936, 5128, True, 9, 3),
+]
+
+
+# (M, N, K, n, d, ring, tile configuration, K slices): InterDecom
+# ReduceScatters with sends whose sub-GEMMs (M / d rows) reach every tile with
+# the row map, the epilogue gate, the done counts and written-through stores,
+# whole and split. The plan is held to these too.
+DECOMP_RS_SIZES = [
+    (4096, 6352, 264, 4, 2, "single", 0, 1), (4096, 2512, 4104, 4, 2, "double", 0, 3),
+    (3072, 2752, 136, 8, 2, "double", 1, 1),
+    (4096, 4432, 136, 4, 2, "single", 2, 1), (4096, 2272, 4104, 8, 2, "double", 2, 2), (2048, 3232, 5128, 4, 2, "single", 2, 3),
+    (4096, 3232, 1032, 4, 2, "double", 3, 1), (3072, 1384, 4104, 4, 2, "single", 3, 3),
+    (4096, 1048, 136, 4, 2, "single", 4, 1), (3072, 1104, 3080, 2, 2, "double", 4, 2),
+    (5120, 3232, 136, 8, 4, "single", 5, 1), (768, 264, 3080, 4, 4, "double", 6, 5), (768, 264, 264, 4, 4, "single", 7, 1),
+    (4096, 4192, 136, 8, 2, "double", 8, 1), (1152, 4192, 4104, 4, 2, "double", 8, 3),
+    (3072, 2752, 264, 4, 2, "single", 9, 1), (3072, 1328, 4104, 4, 2, "double", 9, 3),
 ]
 
 

@@ -28,11 +28,12 @@ def test_work_item_decode_is_a_bijection(tmp_path):
 
 @pytest.mark.skipif(shutil.which("g++") is None, reason="needs a host C++ compiler")
 def test_launch_plans_stay_in_bounds_and_take_every_position(tmp_path):
-    from tests.gpu_helpers import PLAN_SIZES
+    from tests.gpu_helpers import DECOMP_RS_SIZES, PLAN_SIZES
     exe = tmp_path / "plan_check"
     subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", f"-I{CSRC}", "-o", str(exe),
                     os.path.join(HERE, "plan_check.cpp")], check=True)
     sizes = [",".join(str(int(v)) for v in x) for x in PLAN_SIZES]
+    sizes += [f"{M // d},{N},{K},1,{cfg},{split}" for M, N, K, n, d, ring, cfg, split in DECOMP_RS_SIZES]
     out = subprocess.run([str(exe)] + sizes, capture_output=True, text=True, timeout=120)
     assert out.returncode == 0, out.stdout + out.stderr
     assert out.stdout.startswith("ok "), out.stdout

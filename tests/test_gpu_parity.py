@@ -13,7 +13,8 @@ pytestmark = pytest.mark.gpu
 import oracle as O  # noqa: E402
 from paper_2609_10549_amd import compass as C  # noqa: E402
 from synth import make_ag_inputs, make_int_ag_inputs, make_int_rs_inputs, make_rs_inputs  # noqa: E402
-from tests.gpu_helpers import FEW_ROW_SIZES, PLAN_SIZES, TOL, AGCase, RSCase, host_bits, host_f64, rel_err, dev_bits  # noqa: E402
+from tests.gpu_helpers import (DECOMP_RS_SIZES, FEW_ROW_SIZES, PLAN_SIZES, TILE_SHAPES, TOL, AGCase, RSCase, dev_bits, host_bits,  # noqa: E402
+                               host_f64, rel_err)
 
 FAST = C.links(200e9, 200e9)   # emulated link rates for functional tests
 
@@ -70,7 +71,8 @@ def test_gemm_with_partial_integer_exact():
 # ------------------------------------------------------------ split K (few tiles, deep K)
 @pytest.mark.parametrize("with_p", [False, True])
 def test_split_k_integer_exact(with_p):
-    # 2 x 5 tiles of 128 x 128 against 512 workgroup slots: K = 8192 is split
+    # 2 x 5 tiles of 128 x 128 (COMPASS_OPT_TILE) against 512 workgroup slots:
+    # K = 8192 is split into 8 slices
     M, N, K = 256, 520, 8192
     _say("split-k int", with_p)
     if with_p:
@@ -83,11 +85,18 @@ def test_split_k_integer_exact(with_p):
         A, W = dev_bits(inp["shards"][0]), dev_bits(inp["W"])
         P = None
         ref = O.ag_gemm([O.bf16_to_f64(inp["shards"][0])], O.bf16_to_f64(inp["W"]))
-    for rep in range(2):   # the tile counters must be back at zero for the second call
-        Cm = torch.zeros((M, N), dtype=torch.int16, device="cuda")
-        C.compass_gemm(A, W, Cm, P)
-        torch.cuda.synchronize()
-        assert np.array_equal(host_bits(Cm), O.f64_to_bf16_rne(ref)), rep
+    C.compass_set_option(C.OPT_TILE, 2)
+    C.compass_set_option(C.OPT_TILE_TRACE, 1024)
+    try:
+        for rep in range(2):   # the tile counters must be back at zero for the second call
+            Cm = torch.zeros((M, N), dtype=torch.int16, device="cuda")
+            C.compass_gemm(A, W, Cm, P)
+            torch.cuda.synchronize()
+            assert len(C.compass_tile_trace(1024)) == 10 * 8
+            assert np.array_equal(host_bits(Cm), O.f64_to_bf16_rne(ref)), rep
+    finally:
+        C.compass_set_option(C.OPT_TILE_TRACE, 0)
+        C.compass_set_option(C.OPT_TILE, 0)
 
 
 def test_split_k_random_close_to_unsplit():
@@ -143,16 +152,25 @@ def test_split_k_five_to_eight_slices_integer_exact(K, slices, partial):
 
 
 def test_decomp_d16_split_integer_exact():
-    # sub-GEMMs of 64 rows: one row tile each, K split
+    # sub-GEMMs of 64 rows: one row tile of 128 (COMPASS_OPT_TILE) each, three
+    # column tiles, K split into four slices; without the option, whole 64 x 64 tiles
     n, d = 8, 16
     M, N, K = 1024, 264, 2048
     inp = make_int_ag_inputs(M, N, K, n, seed=63)
     ref = O.f64_to_bf16_rne(O.decomp_ag([O.bf16_to_f64(s) for s in inp["shards"]], O.bf16_to_f64(inp["W"]), d))
-    case = AGCase(inp, 3, "single")
-    _say("decomp d16 split")
-    C.compass_decomp_gemm(case.problem, d, FAST)
-    C.compass_sync()
-    assert np.array_equal(host_bits(case.C), ref)
+    for tile, records in ((2, d * 3 * 4), (0, d * 5)):
+        case = AGCase(inp, 3, "single")
+        _say("decomp d16 split", tile)
+        C.compass_set_option(C.OPT_TILE, tile)
+        C.compass_set_option(C.OPT_TILE_TRACE, 1024)
+        try:
+            C.compass_decomp_gemm(case.problem, d, FAST)
+            C.compass_sync()
+            assert len(C.compass_tile_trace(1024)) == records
+        finally:
+            C.compass_set_option(C.OPT_TILE_TRACE, 0)
+            C.compass_set_option(C.OPT_TILE, 0)
+        assert np.array_equal(host_bits(case.C), ref), tile
 
 
 # ------------------------------------------------------------ fused AllGather+GEMM
@@ -472,6 +490,33 @@ def test_decomp_rs_integer_exact(d, ring):
         assert np.array_equal(host_bits(case.send[q]), ref[q * rows:(q + 1) * rows])
 
 
+@pytest.mark.parametrize("M,N,K,n,d,ring,cfg,split", DECOMP_RS_SIZES)
+def test_decomp_rs_every_tile_integer_exact(M, N, K, n, d, ring, cfg, split):
+    inp = make_int_rs_inputs(M, N, K, n, seed=M + N + K)
+    ref = O.f64_to_bf16_rne(O.decomp_rs(O.bf16_to_f64(inp["A"]), O.bf16_to_f64(inp["W"]),
+                                        [p.astype(np.float64) for p in inp["P_in"]], n, d))
+    rank, rows = 1, M // n
+    case = RSCase(inp, rank, ring)
+    for x in [case.C, *(s for s in case.send if s is not None)]:
+        x.fill_(0x7FC0)
+    case.stage.fill_(float("nan"))
+    torch.cuda.synchronize()
+    _say("decomp rs tiles", M, N, K, n, d, ring, cfg, split)
+    C.compass_set_option(C.OPT_TILE_TRACE, 8192)
+    try:
+        C.compass_decomp_gemm(case.problem, d, C.links(0.0, 0.0))
+        C.compass_sync()
+        records = len(C.compass_tile_trace(8192))
+    finally:
+        C.compass_set_option(C.OPT_TILE_TRACE, 0)
+    bm, bn = TILE_SHAPES[cfg]
+    assert records == d * -(-(M // d) // bm) * -(-N // bn) * split
+    assert np.array_equal(host_bits(case.C), ref)
+    for q in range(n):
+        if q != rank:
+            assert np.array_equal(host_bits(case.send[q]), ref[q * rows:(q + 1) * rows]), f"send {q}"
+
+
 def test_decomp_rejects_bad_degree():
     inp = make_int_ag_inputs(512, 64, 64, 4, seed=1)
     case = AGCase(inp, 0, "single")
@@ -789,17 +834,19 @@ def test_paced_link_never_beats_its_rate():
 
 
 def test_tile_trace_records_every_work_item():
-    M, N, K = 512, 384, 4096          # 4 x 3 tiles of 128 x 128, K split
+    M, N, K = 512, 384, 4096          # 4 x 3 tiles of 128 x 128 (COMPASS_OPT_TILE), K in 8 slices
     inp = make_int_ag_inputs(M, N, K, 1, seed=65)
     A, W = dev_bits(inp["shards"][0]), dev_bits(inp["W"])
     Cm = torch.zeros((M, N), dtype=torch.int16, device="cuda")
+    C.compass_set_option(C.OPT_TILE, 2)
     C.compass_set_option(C.OPT_TILE_TRACE, 4096)
     try:
         C.compass_gemm(A, W, Cm)
         rec = C.compass_tile_trace(4096)
     finally:
         C.compass_set_option(C.OPT_TILE_TRACE, 0)
-    assert len(rec) >= 12 and len(rec) % 12 == 0          # tiles x K slices
+        C.compass_set_option(C.OPT_TILE, 0)
+    assert len(rec) == 12 * 8                               # tiles x K slices
     assert sorted(rec[:, 0].tolist()) == list(range(len(rec)))
     t = rec[:, 4:8].astype(np.int64)
     d = (t[:, 1:] - t[:, :-1]) % (1 << 32)                  # ticket <= gate <= loop <= end

@@ -83,6 +83,7 @@ struct GemmParams {
     // 1: no tickets. Workgroup b takes work position static_position(b, j) in
     // its round j (a launch whose tiles wait for nothing finishes them in step,
     // and the next position is known without an atomic round trip)
+    // 2: one round whose positions arrive one after another
     int fixed;
     // first-ticket spreading: the second workgroup on a CU (by HW_ID) takes
     // its first ticket only once `spread_wait` tickets of its queue are gone
@@ -170,8 +171,18 @@ __host__ __device__ inline int work_items(const GemmParams &p) {
 // the round has none for it. A round deals the next grid positions, or those
 // that are left, to the XCDs (b % 8) in consecutive runs of equal length, give
 // or take one, so that the tiles an XCD holds at a time share rows and columns.
+// A fused AllGather's one round with two workgroups to a CU (fixed == 2) deals
+// them group_m at a time (one column of a row-tile group), those that fill no
+// turn over the XCDs one by one: the tiles of one arriving partition are
+// consecutive, and in long runs they would share the CUs of a few XCDs while
+// the others wait.
 __host__ __device__ inline int static_position(const GemmParams &p, int b, int j) {
     const int first = j * p.grid, all = work_items(p);
+    if (p.fixed == 2) {
+        const int v = b % kMaxQueues, c = b / kMaxQueues, whole = all / (kMaxQueues * p.group_m) * p.group_m;
+        if (j > 0 || b >= all) return -1;
+        return c < whole ? (v + kMaxQueues * (c / p.group_m)) * p.group_m + c % p.group_m : b;
+    }
     const int left = all - first < p.grid ? all - first : p.grid;
     if (left <= 0) return -1;
     const int v = b % kMaxQueues, c = b / kMaxQueues;

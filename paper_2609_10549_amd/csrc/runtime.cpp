@@ -2017,7 +2017,10 @@ int op_ag_gemm(const compass_problem *p, const compass_links *l, void *stream) {
     g.nparts = geo.P;
     g.resident_mask = resident_mask(p, geo);
     g.start_word = &g_ctx.hw[kHwStart];
-    g.fixed = g.spread_wait == 0 && work_items(g) <= g.grid;
+    // one round: in runs while every tile has a CU of its own (4896 x 384 x
+    // 11912, 234 tiles: 281 us in runs, 288 dealt over the XCDs), dealt when two
+    // share one (2240 x 3528 x 11440, 504 tiles: 436 / 390)
+    if (g.spread_wait == 0 && work_items(g) <= g.grid) g.fixed = work_items(g) > g_ctx.num_cu ? 2 : 1;
     submit(0, std::move(ag[0]));
     submit(1, std::move(ag[1]));
     return launch(g, cfg, false, s);

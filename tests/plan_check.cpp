@@ -66,15 +66,25 @@ static bool check(int M, int N, int K, bool partial, const PlanLimits &lim, char
             if (c < cost * (1 - 1e-9)) { std::sprintf(why, "plan %d/%d at %.2f us, %d/%d at %.2f", pl.cfg, pl.split, cost, cfg, sp, c); return false; }
         }
     const int all = work_items(g);
-    std::vector<char> seen(all, 0);
-    for (int b = 0; b < g.grid; ++b)
-        for (int j = 0;; ++j) {
-            const int pos = static_position(g, b, j);
-            if (pos < 0) break;
-            if (pos >= all || seen[pos]++) { std::sprintf(why, "position %d of %d by workgroup %d round %d", pos, all, b, j); return false; }
+    for (int fixed = 1; fixed <= 2; ++fixed) {
+        GemmParams f = g;
+        f.fixed = fixed;
+        std::vector<int> by(all, -1);   // workgroup of each position
+        for (int b = 0; b < f.grid; ++b)
+            for (int j = 0; fixed == 1 || j < 2; ++j) {
+                const int pos = static_position(f, b, j);
+                if (pos < 0) break;
+                if (pos >= all || by[pos] >= 0) { std::sprintf(why, "position %d of %d by workgroup %d round %d", pos, all, b, j); return false; }
+                by[pos] = b;
+            }
+        if (fixed == 2 && all > f.grid) continue;   // (only launches of one round are dealt so)
+        for (int p = 0; p < all; ++p) {
+            if (by[p] < 0) { std::sprintf(why, "position %d of %d left out", p, all); return false; }
+            // dealt group_m at a time over the XCDs, as long as the turns are full
+            if (fixed == 2 && p < all / (kMaxQueues * f.group_m) * kMaxQueues * f.group_m &&
+                by[p] % kMaxQueues != p / f.group_m % kMaxQueues) { std::sprintf(why, "position %d on XCD %d", p, by[p] % kMaxQueues); return false; }
         }
-    for (int p = 0; p < all; ++p)
-        if (!seen[p]) { std::sprintf(why, "position %d of %d left out", p, all); return false; }
+    }
     return true;
 }
 

@@ -317,6 +317,30 @@ def test_ag_gemm_tail_split_128_tiles_option_on_small_launches(min_k, records):
     assert counts[min_k] == (records or counts[0])
 
 
+def test_ag_gemm_one_round_deals_a_partition_over_every_xcd():
+    # 18 x 28 tiles of 128 x 128 in one round of 512 workgroups: the 28 tiles
+    # of a row tile start with its partition's arrival, so they must not share
+    # a few XCDs (the tile trace has the XCD of every tile; the last two row
+    # tiles of the ready order are a group of their own, dealt one by one)
+    M, N, K, n = 2240, 3528, 520, 4
+    inp = make_int_ag_inputs(M, N, K, n, seed=43)
+    ref = O.f64_to_bf16_rne(O.ag_gemm([O.bf16_to_f64(s) for s in inp["shards"]], O.bf16_to_f64(inp["W"])))
+    case = AGCase(inp, 3, "double")
+    case.C.fill_(0x7FC0)
+    _say("ag one round", M, N, K)
+    C.compass_set_option(C.OPT_TILE_TRACE, 1024)
+    try:
+        C.compass_ag_gemm(case.problem, FAST)
+        C.compass_sync()
+        rec = C.compass_tile_trace(1024)
+    finally:
+        C.compass_set_option(C.OPT_TILE_TRACE, 0)
+    assert len(rec) == 18 * 28
+    assert np.array_equal(host_bits(case.C), ref)
+    row, xcc = rec[:, 1] >> 16, rec[:, 3] & 7
+    assert sum(len(set(xcc[row == r].tolist())) == 8 for r in range(18)) >= 16
+
+
 def test_ag_gemm_config1_all_ranks():
     # AllGather-GEMM, TP=2: shards 256x512 U[-1,1], B 512x1024, single ring
     inp = make_ag_inputs(512, 1024, 512, 2, seed=1, dist_a=("uniform", -1.0, 1.0), dist_w=("uniform", -1.0, 1.0))

@@ -782,18 +782,17 @@ void gemm_kernel(const GemmParams p) {
 
         if (wt) __builtin_amdgcn_s_waitcnt(0);   // write-through stores acknowledged
         __syncthreads();   // stores issued and complete; LDS free for the next tile
-        if (RS && finish && p.done_host && !failed && tid == 0) {
-            uint64_t dm = touch & p.send_mask;
-            if (dm) {
-                while (dm) {
-                    const int q = __builtin_ctzll(dm);
-                    const uint32_t old = __hip_atomic_fetch_add(&p.done_cnt[p.flag_base + q], 1u,
-                                                                __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    if (old + 1u == p.done_expect[q])
-                        __hip_atomic_store(&p.done_host[p.flag_base + q], p.epoch, __ATOMIC_RELEASE,
-                                           __HIP_MEMORY_SCOPE_SYSTEM);
-                    dm &= dm - 1;
-                }
+        if (RS && finish && p.done_host && !failed && tid < 64) {
+            // lane q counts for partition q, so that the counts' round trips
+            // overlap: a tile of an InterDecom sub-operator counts for every
+            // partition that is sent (4096 x 2048 x 4096, 8 ranks, double ring,
+            // d = 4, 128 x 64 tiles: 370 -> 242 us)
+            if (((touch & p.send_mask) >> lane) & 1ull) {
+                const int f = p.flag_base + lane;
+                const uint32_t old = __hip_atomic_fetch_add(&p.done_cnt[f], 1u, __ATOMIC_RELAXED,
+                                                            __HIP_MEMORY_SCOPE_AGENT);
+                if (old + 1u == p.done_expect[lane])
+                    __hip_atomic_store(&p.done_host[f], p.epoch, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
             }
         }
         if (traced && tid == 0) {

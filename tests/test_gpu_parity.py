@@ -541,6 +541,35 @@ def test_decomp_rs_every_tile_integer_exact(M, N, K, n, d, ring, cfg, split):
             assert np.array_equal(host_bits(case.send[q]), ref[q * rows:(q + 1) * rows]), f"send {q}"
 
 
+def test_decomp_rs_counts_every_partition_at_once():
+    # a tile of a sub-operator counts for all 30 partitions that are sent. What
+    # follows its gate (the partial added, C written through, the counts) took
+    # 84 us with the counts one after another, each an atomic's round trip, and
+    # takes 3 with one per lane; 20 us lies well clear of both
+    M, N, K, n = 1024, 2048, 264, 16
+    inp = make_int_rs_inputs(M, N, K, n, seed=46)
+    ref = O.f64_to_bf16_rne(O.decomp_rs(O.bf16_to_f64(inp["A"]), O.bf16_to_f64(inp["W"]),
+                                        [p.astype(np.float64) for p in inp["P_in"]], n, 1))
+    case = RSCase(inp, 5, "double")
+    _say("decomp rs counts", M, N, K, n)
+    C.compass_set_option(C.OPT_TILE_TRACE, 2048)
+    try:
+        C.compass_decomp_gemm(case.problem, 1, C.links(0.0, 0.0))
+        C.compass_sync()
+        rec = C.compass_tile_trace(2048)
+    finally:
+        C.compass_set_option(C.OPT_TILE_TRACE, 0)
+    assert np.array_equal(host_bits(case.C), ref)
+    rows = M // n
+    for q in range(n):
+        if q != 5:
+            assert np.array_equal(host_bits(case.send[q]), ref[q * rows:(q + 1) * rows]), f"send {q}"
+    t = rec[:, 4:8].astype(np.int64)
+    after_gate = np.median((t[:, 3] - t[:, 1]) % (1 << 32)) * 0.01   # 100 MHz counter
+    _say("us after the gate", after_gate)
+    assert after_gate < 20.0
+
+
 def test_decomp_rejects_bad_degree():
     inp = make_int_ag_inputs(512, 64, 64, 4, seed=1)
     case = AGCase(inp, 0, "single")

@@ -108,11 +108,20 @@ inline Plan plan_gemm(int M, int N, int K, bool partial, const PlanLimits &lim) 
 // Tile of a fused operator so small that tiles of at most 128 x 128 fit one
 // round of workgroups; -1 when no such tile's do. Every tile then starts with
 // the launch, and what follows the last arrival is one tile, so the estimate's
-// cheapest is the shortest tail: 512 x 1024 x 512 over two ranks 25.4 us in
-// 128 x 128 tiles (32 CUs busy), 22.0 in 64 x 64. (Larger tiles in one round
-// wait for more of the arrivals and leave a longer tail: the MLP fc1 218 us in
-// 256 x 256 tiles, 190 in two rounds of 256 x 128.)
+// cheapest is the shortest tail. (Larger tiles in one round wait for more of
+// the arrivals and leave a longer tail: the MLP fc1 218 us in 256 x 256 tiles,
+// 190 in two rounds of 256 x 128.)
+//
+// An AllGather whose 64 x 64 tiles have a CU each takes those: the estimate's
+// costs are those of a busy chip, and below some 30 stages they put 128 x 64
+// first, which in 19 sizes of K = 64 to 2048 was never the faster by more than
+// 0.3 us (512 x 1024 x 512 over two ranks 20.8 us against 22.1, in 128 x 128
+// 24.0; 1024 x 1024 x 1024 over four 30.8 against 32.6). With two of them on a
+// CU they no longer are (1024 x 2048 x 512: 33.9 against 28.1). For a
+// ReduceScatter, whose last sends follow the launch, either is within 1.5 %.
 inline int plan_one_round(int M, int N, int K, bool partial, const PlanLimits &lim) {
+    const long tiles64 = (long)((M + 63) / 64) * ((N + 63) / 64);
+    if (!partial && tiles64 <= lim.num_cu && (lim.slots_override <= 0 || tiles64 <= lim.slots_override)) return kTile64;
     int best = -1;
     double tb = 1e30;
     for (int cfg = 0; cfg < kTileCfgs; ++cfg) {

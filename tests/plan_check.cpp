@@ -2,8 +2,9 @@
 // (kernel_params.h: static_position): over a grid of GEMM sizes, odd ones among
 // them, the plan's row tiles fit the row-tile table, a split fits one round of
 // workgroups, the split counters and the workspace, no slice is empty, no plan
-// within these bounds has a lower estimate, and the rounds of all workgroups
-// take every work position once. The sizes given as
+// within these bounds has a lower estimate, the rounds of all workgroups take
+// every work position once, and fused operators of one round get the tile that
+// plan_one_round describes. The sizes given as
 // arguments ("M,N,K,partial,cfg,split") must get that tile and split.
 // Prints "ok <sizes>" or the first failure.
 #include <cstdio>
@@ -88,9 +89,35 @@ static bool check(int M, int N, int K, bool partial, const PlanLimits &lim, char
     return true;
 }
 
+// The tile of a fused operator of one round: 64 x 64 for an AllGather whose
+// tiles of that size have a CU each, else the lowest estimate among the tiles of
+// at most 128 x 128 that fit.
+static bool check_one_round(int M, int N, int K, bool partial, const PlanLimits &lim, char *why) {
+    const int cfg = plan_one_round(M, N, K, partial, lim);
+    auto tiles = [&](int c) {
+        return (long)((M + kTileShapes[c].rows - 1) / kTileShapes[c].rows) * ((N + kTileShapes[c].cols - 1) / kTileShapes[c].cols);
+    };
+    auto fits = [&](int c) {
+        const TileShape &ts = kTileShapes[c];
+        return ts.rows <= 128 && ts.cols <= 128 && (M + ts.rows - 1) / ts.rows <= kMaxRowTiles &&
+               tiles(c) <= (lim.slots_override > 0 ? lim.slots_override : (long)lim.num_cu * ts.wg_per_cu);
+    };
+    if (cfg >= 0 && !fits(cfg)) { std::sprintf(why, "one round in tile %d", cfg); return false; }
+    if (!partial && fits(kTile64) && tiles(kTile64) <= lim.num_cu) {
+        if (cfg != kTile64) std::sprintf(why, "tile %d, not 64 x 64 with a CU each", cfg);
+        return cfg == kTile64;
+    }
+    for (int c = 0; c < kTileCfgs; ++c)
+        if (fits(c) && (cfg < 0 || plan_cost(c, 1, M, N, K, partial, lim) < plan_cost(cfg, 1, M, N, K, partial, lim) * (1 - 1e-9))) {
+            std::sprintf(why, "one round in tile %d, cheaper in %d", cfg, c);
+            return false;
+        }
+    return true;
+}
+
 int main(int argc, char **argv) {
     const PlanLimits split{256, 0, 3ull * 256 * 256 * 256 * 4}, whole{256, 0, 0}, small{4, 0, 3ull * 4 * 256 * 256 * 4},
-                     stage128{256, 0, split.split_bytes, 128, 8.0}, stage192{256, 0, split.split_bytes, 192, 8.0};
+                     few{256, 24, 0}, stage128{256, 0, split.split_bytes, 128, 8.0}, stage192{256, 0, split.split_bytes, 192, 8.0};
     char why[256];
     int count = 0;
     const int Ms[] = {1, 15, 64, 65, 127, 129, 257, 640, 1000, 2049, 4096, 8191, 32768, 32769, 65536};
@@ -102,11 +129,15 @@ int main(int argc, char **argv) {
                 for (int p = 0; p < 2; ++p)
                     for (const PlanLimits &lim : {split, whole, small, stage128, stage192}) {
                         ++count;
-                        if (!check(M, N, K, p, lim, why)) {
+                        if (!check(M, N, K, p, lim, why) || !check_one_round(M, N, K, p, lim, why)) {
                             std::printf("FAIL %d x %d x %d partial %d cus %d: %s\n", M, N, K, p, lim.num_cu, why);
                             return 1;
                         }
                     }
+    for (const int *x : {(const int[]){512, 1024, 512}, (const int[]){1000, 1000, 520}, (const int[]){256, 256, 64}}) {
+        for (const PlanLimits &lim : {split, few})
+            if (!check_one_round(x[0], x[1], x[2], false, lim, why)) { std::printf("FAIL %d x %d x %d: %s\n", x[0], x[1], x[2], why); return 1; }
+    }
     for (int i = 1; i < argc; ++i) {
         int M, N, K, p, cfg, sp;
         if (std::sscanf(argv[i], "%d,%d,%d,%d,%d,%d", &M, &N, &K, &p, &cfg, &sp) != 6) { std::printf("FAIL argument %s\n", argv[i]); return 1; }

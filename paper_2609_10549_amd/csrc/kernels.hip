@@ -508,11 +508,17 @@ void gemm_kernel(const GemmParams p) {
         }
 
         if (traced && tid == 0) t_loop = rtc32();
-        // fetch the next ticket while the epilogue runs
-        if (!p.fixed && tid == 0) {
-            const uint32_t c = __hip_atomic_fetch_add(&p.ctrl[v], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            s_pos = ticket_position(p, v, c);
-        }
+        // The next ticket is fetched while the epilogue runs, but behind its gate:
+        // a workgroup that waits for a late partition would hold back a tile that
+        // others are free to take (ReduceScatter 6144 x 3000 x 5000, 8 ranks at
+        // 100 / 50 GB/s: 751 us with the ticket taken before the gate, 665 behind)
+        auto next_ticket = [&]() {
+            if (!p.fixed && tid == 0) {
+                const uint32_t c = __hip_atomic_fetch_add(&p.ctrl[v], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                s_pos = ticket_position(p, v, c);
+            }
+        };
+        if (!RS) next_ticket();
 
         // thread coordinates the compiler cannot see to be the same for every
         // tile: addresses derived from them are computed where they are used,
@@ -604,6 +610,7 @@ void gemm_kernel(const GemmParams p) {
             if (!s_ok) failed = true;
             known |= need;
         }
+        if (RS) next_ticket();
         if (RS && traced && tid == 0) t_gate = rtc32();
 
         if (finish) {

@@ -444,6 +444,42 @@ def test_gemm_rs_first_step_partial_sources_integer_exact(ring, source):
             assert np.array_equal(host_bits(case.send[q]), ref[q * rows:(q + 1) * rows]), f"send {q}"
 
 
+@pytest.mark.parametrize("fwd,bwd", [(20e9, 0.1e9), (0.1e9, 20e9)])
+def test_gemm_rs_a_waiting_workgroup_holds_no_tile_back(fwd, bwd):
+    # 8 tiles of 128 x 128 on three workgroups: the partials of two row tiles are
+    # in place, one row tile's lands at once, the other's after 1.3 ms. The
+    # workgroup that need not wait computes every other tile meanwhile, also those
+    # that come after the late row tile's two
+    M, N, K, n = 512, 256, 64, 2
+    inp = make_int_rs_inputs(M, N, K, n, seed=47)
+    ref = O.f64_to_bf16_rne(O.gemm_rs(O.bf16_to_f64(inp["A"]), O.bf16_to_f64(inp["W"]),
+                                      [p.astype(np.float64) for p in inp["P_in"]], n))
+    case = RSCase(inp, 0, "double")
+    _say("rs waiting workgroups", fwd, bwd)
+    C.compass_set_option(C.OPT_TILE, 2)
+    C.compass_set_option(C.OPT_GRID, 3)
+    try:
+        C.compass_gemm_rs(case.problem, C.links(fwd, bwd))   # (first copies of new memory may be late)
+        C.compass_sync()
+        C.compass_set_option(C.OPT_TILE_TRACE, 64)
+        C.compass_gemm_rs(case.problem, C.links(fwd, bwd))
+        C.compass_sync()
+        rec = C.compass_tile_trace(64).astype(np.int64)
+    finally:
+        C.compass_set_option(C.OPT_TILE_TRACE, 0)
+        C.compass_set_option(C.OPT_GRID, 0)
+        C.compass_set_option(C.OPT_TILE, 0)
+    assert np.array_equal(host_bits(case.C), ref)
+    assert len(rec) == 8
+    since = lambda col: (rec[:, col] - rec[:, 4].min()) % (1 << 32)   # noqa: E731
+    gate, end = since(5), since(7)
+    late = gate > 50000                        # gates passed after 0.5 ms (100 MHz counter)
+    _say("gates", gate.tolist(), "ends", end.tolist(), "row tiles", (rec[:, 1] >> 16).tolist())
+    assert late.sum() == 2
+    assert len(set((rec[late, 1] >> 16).tolist())) == 1
+    assert end[~late].max() < gate[late].min()
+
+
 @pytest.mark.parametrize("ring", ["single", "double"])
 def test_gemm_rs_pinned_host_partials_and_sends_integer_exact(ring):
     # every remote buffer of the ReduceScatter in pinned host memory: the

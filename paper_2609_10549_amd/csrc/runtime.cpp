@@ -2004,9 +2004,13 @@ int op_ag_gemm(const compass_problem *p, const compass_links *l, void *stream) {
     const double lam = lambda_estimate(p, geo, l);
     const int cfg = pick_tile(p->M, p->N, p->K, geo.fb != 0.5 && geo.sub == 1 ? geo.rows : min_part_rows(geo), lam, false);
     if ((rc = set_shape(g, cfg, p->M, p->N, p->K, p->gathered, p->M, p->W, p->C, nullptr)) != COMPASS_OK) return rc;
-    // 256-row tiles: one row-tile group per partition, so that the dealing
-    // and the tail split follow partitions
-    if (tile_rows(cfg) == 256 && geo.sub == 1 && geo.fb == 0.5 && min_part_rows(geo) % 256 == 0)
+    // 256 x 256 tiles: one row-tile group per partition, so that the dealing
+    // and the tail split follow partitions. (256 x 128 tiles, which do not split,
+    // keep groups of 4: with one group per partition W is read once per
+    // partition, 2048 x 11264 x 1024 over 4 ranks 88 against 80 us, 4096 x 8064 x
+    // 4096 over 8 284 against 269, and where a partition holds two row tiles it is
+    // as fast.)
+    if (cfg == kTile256 && geo.sub == 1 && geo.fb == 0.5 && min_part_rows(geo) % 256 == 0)
         g.group_m = std::max(1, std::min(4, min_part_rows(geo) / 256));
     double arrive[2 * kMaxRanks];
     if ((rc = expected_arrivals(p, geo, l, resident_mask(p, geo), arrive)) != COMPASS_OK) return rc;

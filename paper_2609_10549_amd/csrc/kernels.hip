@@ -27,14 +27,14 @@
 // XOR-permuted with (r >> 1) & 7, so a fragment read hits distinct banks.
 //
 // What bounds it: the large tiles, the matrix cores at the clock the chip's
-// power allows (1.4 - 1.55 GHz under this load, 2.4 GHz nominal), so what
+// power allows (1.5 - 1.7 GHz under this load, 2.4 GHz nominal), so what
 // counts is energy per flop and cycles lost to waits. 8192 x 6144 x 12288,
 // 256 x 256 tiles, each step against the one before it on one box:
 //  - three A buffers in place of two (loads have 1 to 1.75 stages to land; one
 //    barrier per stage): 942 -> 925 us;
 //  - LDS reads and global loads one at a time between the MFMAs in place of
 //    bursts of eight, which filled their queues and held up the MFMAs behind
-//    them (matrix cores 75 -> 80 % busy): 925 -> 908 us;
+//    them: 925 -> 908 us;
 //  - v_mfma_f32_16x16x32_bf16 in place of 32x32x16: half the accumulator
 //    traffic per flop (each accumulator is read and written once per 32 of K
 //    in place of 16), a higher clock and shorter stalls: 908 -> 834 us
@@ -572,7 +572,7 @@ void gemm_kernel(const GemmParams p) {
         };
         const bool has_p = RS && p.P != nullptr;
 
-        // split K: every slice stores its partial tile (fp32, row-major);
+        // split K: every slice stores its partial tile (fp32);
         // the slice that completes the tile's count sums all of them in
         // slice order, so the result does not depend on which one was last
         bool finish = true;

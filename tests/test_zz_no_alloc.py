@@ -1,10 +1,10 @@
 """compass_gemm_noalloc, the plain GEMM for callers that cannot allocate,
 against compass_gemm through the C ABI: two calls in a row, the second on a
-smaller input, so the shared scratch's ticket queues must start each launch
-cleared. Integer-valued inputs (every fp32 partial sum exact) must give the
-same bits as compass_gemm and as the oracle's exact product rounded once;
-seeded normal inputs must stay within 5e-3 normwise of the fp64 oracle (the
-two entry points may sum K in different slice orders)."""
+smaller input, so nothing of the first may be left to the second. Integer-valued
+inputs (every fp32 partial sum exact) must give the same bits as compass_gemm
+and as the oracle's exact product rounded once; seeded normal inputs must stay
+within 5e-3 normwise of the fp64 oracle (the two entry points may sum K in
+different slice orders)."""
 from __future__ import annotations
 
 import numpy as np
@@ -16,8 +16,8 @@ from synth import make_ag_inputs, make_int_ag_inputs, make_int_rs_inputs
 
 BF16_NAN = 0x7FC0
 
-# (M, N, K): a 256 x 256-tile shape with ragged edges, then a smaller
-# 128 x 128-tile one; the GPT-3 AllGather shape, then a small one
+# (M, N, K): a launch of several hundred tiles with ragged edges, then one of a
+# few; the GPT-3 AllGather shape (256 x 256 tiles, three rounds), then a small one
 PAIRS = [((1544, 1048, 520), (264, 136, 200)), ((8192, 6144, 12288), (520, 264, 136))]
 
 
